@@ -13,9 +13,8 @@
 // is the MFMA "A" operand and the activation tile the "B" operand, so each
 // lane's accumulator holds 4 consecutive output columns of one row. Large
 // products run on a persistent kernel (one block per CU walking 256x256 tiles,
-// see gemm_bf16_p4); the others on one block per tile with operands staged
-// global -> registers -> LDS (rows padded by 16 bytes, no bank conflicts),
-// double-buffered, prefetched one K step ahead. Tiles are numbered so that each
+// see gemm_bf16_p4); the others on one block per tile of 32x32 to 128x128
+// (gemm_bf16_ring). Tiles are numbered so that each
 // of the 8 XCDs (the hardware deals workgroup b to XCD b % 8) works through a
 // contiguous range of them, walked in groups of row blocks so that operand
 // blocks are reused from that XCD's L2.
@@ -81,132 +80,229 @@ __device__ __forceinline__ float resid4(const u32x2& raw, int e, LnRow st, float
   return 0.f;
 }
 
-constexpr int GM = 128, GN = 128, GK = 64, GLD = GK + 8;
-
+// Epilogue and stores of one 32x32 accumulator: element v is column
+// nb + 8 (v / 4) + v % 4 of row m (the lane's hi half already in nb).
 template <int EPI>
-__global__ __launch_bounds__(256, 2) void gemm_bf16_mfma(const bf16* __restrict__ A, int lda,
-                                                          const bf16* __restrict__ Bt, const float* __restrict__ bias,
-                                                          const void* __restrict__ R, int ldr, void* __restrict__ C,
-                                                          int ldc, int M, int N, int K, int tiles_n, int n_tiles,
-                                                          LnResid ln) {
-  __shared__ __attribute__((aligned(16))) bf16 sA[2][GM * GLD];
-  __shared__ __attribute__((aligned(16))) bf16 sB[2][GN * GLD];
-
-  const int per_xcd = (n_tiles + 7) >> 3;
-  const int t = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-  if (t >= n_tiles) return;
-  const int m0 = (t / tiles_n) * GM, n0 = (t % tiles_n) * GN;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int l32 = lane & 31, hi = lane >> 5;
-
-  // global -> register staging: 128 rows x 8 chunks of 16 B per operand, 4 chunks per thread
-  bf16x8 ra[4], rb[4];
-  auto gload = [&](int k0) {
+__device__ __forceinline__ void store_acc(const floatx16& acc, int m, int nb, const float* __restrict__ bias,
+                                          const void* __restrict__ R, int ldr, void* __restrict__ C, int ldc,
+                                          const LnResid& ln) {
+  LnRow st{0.f, 0.f};
+  if (EPI == EPI_BIAS_RESLN || epi_lnfold(EPI)) st = ln.stats[m];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int c = tid + 256 * u, r = c >> 3, col = (c & 7) * 8;
-      const int gm = min(m0 + r, M - 1);
-      ra[u] = *reinterpret_cast<const bf16x8*>(A + (size_t)gm * lda + k0 + col);
-      rb[u] = *reinterpret_cast<const bf16x8*>(Bt + (size_t)(n0 + r) * K + k0 + col);
-    }
-  };
-  auto lstore = [&](int buf) {
+  for (int g = 0; g < 4; ++g) {
+    const int n = nb + 8 * g;
+    floatx4 b4 = *reinterpret_cast<const floatx4*>(bias + n);
+    if (epi_lnfold(EPI)) {
+      // the same operations as the persistent kernel's epilogue
+      const floatx4 cs4 = *reinterpret_cast<const floatx4*>(ln.g + n);
+      bf16x4 o;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int c = tid + 256 * u, r = c >> 3, col = (c & 7) * 8;
-      *reinterpret_cast<bf16x8*>(&sA[buf][r * GLD + col]) = ra[u];
-      *reinterpret_cast<bf16x8*>(&sB[buf][r * GLD + col]) = rb[u];
-    }
-  };
-
-  floatx16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  const int nk = K / GK;
-  gload(0);
-  lstore(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) gload((kt + 1) * GK);
-#pragma unroll
-    for (int ks = 0; ks < GK / 16; ++ks) {
-      bf16x8 fw[2], fx[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        fw[i] = *reinterpret_cast<const bf16x8*>(&sB[cur][(wn * 64 + i * 32 + l32) * GLD + ks * 16 + hi * 8]);
-        fx[i] = *reinterpret_cast<const bf16x8*>(&sA[cur][(wm * 64 + i * 32 + l32) * GLD + ks * 16 + hi * 8]);
+      for (int q = 0; q < 4; ++q) {
+        float v = fmaf(acc[4 * g + q], st.x, fmaf(st.y, cs4[q], b4[q]));
+        if (epi_gelu(EPI)) v = gelu_erf(v);
+        o[q] = (bf16)v;
       }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          if (epi_lnfold(EPI))  // fp16 operands (see gemm_bf16_p4)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fw[i]),
-                                                               __builtin_bit_cast(f16x8, fx[j]), acc[i][j], 0, 0, 0);
-          else
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[i], fx[j], acc[i][j], 0, 0, 0);
-        }
-    }
-    if (kt + 1 < nk) lstore(cur ^ 1);
-    __syncthreads();
-  }
-
-  // accumulator (i, j), element v: column n = n0 + wn*64 + i*32 + 8*(v/4) + 4*hi + v%4,
-  // row m = m0 + wm*64 + j*32 + l32
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int m = m0 + wm * 64 + j * 32 + l32;
-    if (m >= M) continue;
-    LnRow st{0.f, 0.f};
-    if (EPI == EPI_BIAS_RESLN || epi_lnfold(EPI)) st = ln.stats[m];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int n = n0 + wn * 64 + i * 32 + 8 * g + 4 * hi;
-        floatx4 b4 = *reinterpret_cast<const floatx4*>(bias + n);
-        if (epi_lnfold(EPI)) {
-          // the same operations as the persistent kernel's epilogue
-          const floatx4 cs4 = *reinterpret_cast<const floatx4*>(ln.g + n);
-          bf16x4 o;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            float v = fmaf(acc[i][j][4 * g + q], st.x, fmaf(st.y, cs4[q], b4[q]));
-            if (epi_gelu(EPI)) v = gelu_erf(v);
-            o[q] = (bf16)v;
-          }
-          *reinterpret_cast<bf16x4*>((bf16*)C + (size_t)m * ldc + n) = o;
-        } else if (epi_resid(EPI)) {
-          const u32x2 raw = *reinterpret_cast<const u32x2*>((const bf16*)R + (size_t)m * ldr + n);
-          floatx4 g4 = {0.f, 0.f, 0.f, 0.f};
-          if (EPI == EPI_BIAS_RESLN) {
-            g4 = *reinterpret_cast<const floatx4*>(ln.g + n);
-            b4 += *reinterpret_cast<const floatx4*>(ln.b + n);
-          }
-          f16x4 o;
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            o[q] = (f16)epilogue<EPI>(acc[i][j][4 * g + q], b4[q], resid4<EPI>(raw, q, st, g4[q]));
-          *reinterpret_cast<f16x4*>((f16*)C + (size_t)m * ldc + n) = o;
-        } else {
-          bf16x4 o;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) o[q] = (bf16)epilogue<EPI>(acc[i][j][4 * g + q], b4[q], 0.f);
-          *reinterpret_cast<bf16x4*>((bf16*)C + (size_t)m * ldc + n) = o;
-        }
+      *reinterpret_cast<bf16x4*>((bf16*)C + (size_t)m * ldc + n) = o;
+    } else if (epi_resid(EPI)) {
+      const u32x2 raw = *reinterpret_cast<const u32x2*>((const bf16*)R + (size_t)m * ldr + n);
+      floatx4 g4 = {0.f, 0.f, 0.f, 0.f};
+      if (EPI == EPI_BIAS_RESLN) {
+        g4 = *reinterpret_cast<const floatx4*>(ln.g + n);
+        b4 += *reinterpret_cast<const floatx4*>(ln.b + n);
       }
+      f16x4 o;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[q] = (f16)epilogue<EPI>(acc[4 * g + q], b4[q], resid4<EPI>(raw, q, st, g4[q]));
+      *reinterpret_cast<f16x4*>((f16*)C + (size_t)m * ldc + n) = o;
+    } else {
+      bf16x4 o;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[q] = (bf16)epilogue<EPI>(acc[4 * g + q], b4[q], 0.f);
+      *reinterpret_cast<bf16x4*>((bf16*)C + (size_t)m * ldc + n) = o;
     }
   }
 }
 
+// s_waitcnt vmcnt(N) (loads of this wave except the N youngest have landed) and lgkmcnt(0), then the block's barrier.
+template <int N>
+struct RingWait {
+  static __device__ __forceinline__ void go() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));  // vmcnt(N) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  }
+};
+template <int S, int I = 0, class F>
+__device__ __forceinline__ void ring_tail(F f) {
+  f(std::integral_constant<int, I>{});
+  if constexpr (I + 1 < S) ring_tail<S, I + 1>(f);
+}
+
+constexpr int RK = 64;  // k columns per stage
+
+// Ring kernel: one block of four waves per BM x BN output tile, for products
+// with too few 256x256 tiles for the persistent kernel. What bounds a small
+// product is the latency of its operand loads and the serial chain of a
+// block's k steps, so the operands travel HBM/L2 -> LDS with
+// buffer_load_dwordx4 ... lds (no registers) through a ring of S stages of 64
+// k columns, S requested ahead, and each k step costs one barrier: stage k + 1
+// has landed (a counted vmcnt) and every wave has read stage k's fragments,
+// so stage k's buffer takes the loads of stage k + S while the fragments of
+// stage k + 1 are read between the MFMAs of stage k. Rows are 128 bytes, 16-byte
+// slot s of row r holding chunk s ^ ((r / 2) % 8) (applied on the global
+// side): conflict-free fragment reads without padding. A wave computes
+// MI x NI MFMA tiles (with the 32x32 and 32x64 tiles only one or two waves
+// compute, all four load). Each output is summed over k in the same order
+// with the same MFMAs as in the persistent kernel, so a score does not depend
+// on which kernel took its batch. Measured per launch, against the kernel this
+// replaced (128x128 tiles, operands through registers, one step ahead): M 34,
+// N 512, K 2048 26 -> 6.3 us; M 34, N 1024, K 4096 48 -> 9.5; M 300 51 -> 12;
+// M 1064 52 -> 21; M 4000 55 -> 37; M 1064, N 3072, K 1024 17.5 -> 11.3.
+template <int EPI, int BM, int BN, int MI, int NI, int S>
+__global__ __launch_bounds__(256) void gemm_bf16_ring(const bf16* __restrict__ A, int lda, const bf16* __restrict__ Bt,
+                                                      const float* __restrict__ bias, const void* __restrict__ R,
+                                                      int ldr, void* __restrict__ C, int ldc, int M, int N, int K,
+                                                      int tiles_m, int tiles_n, bool n_major, LnResid ln) {
+  constexpr int ROWS = BM + BN, LPW = ROWS / 32;  // 1 KB loads per wave and stage
+  constexpr int CWM = BM / (32 * MI), CW = CWM * (BN / (32 * NI));  // waves that compute
+  static_assert(CW >= 1 && CW <= 4 && S >= 4 && S % 2 == 0 && ROWS % 32 == 0, "tile shape");
+  __shared__ __attribute__((aligned(16))) bf16 lds[S * ROWS * RK];
+  typedef __attribute__((address_space(3))) void* lds_ptr_t;
+
+  const int n_tiles = tiles_m * tiles_n, per_xcd = (n_tiles + 7) >> 3;
+  const int t = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+  if (t >= n_tiles) return;
+  const int mt = n_major ? t % tiles_m : t / tiles_n, nt = n_major ? t / tiles_m : t % tiles_n;
+  const int m0 = mt * BM, n0 = nt * BN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hi = lane >> 5;
+
+  const __amdgpu_buffer_rsrc_t ra =
+      __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, (int)(2u * (uint32_t)M * (uint32_t)lda), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rb =
+      __builtin_amdgcn_make_buffer_rsrc((void*)Bt, 0, (int)(2u * (uint32_t)N * (uint32_t)K), 0x00020000);
+  // Load u of a wave fills rows 32 u + 8 wave .. + 7 of the stage (A rows, then
+  // B rows): one byte offset per load, k0 in the scalar offset. Rows past M
+  // lie beyond the A resource; their results are not stored.
+  uint32_t off[LPW];
+#pragma unroll
+  for (int u = 0; u < LPW; ++u) {
+    const int r = 32 * u + 8 * wave + (lane >> 3);
+    const int c = ((lane & 7) ^ ((r >> 1) & 7)) * 16;
+    off[u] = 32 * u < BM ? 2u * (uint32_t)(m0 + r) * (uint32_t)lda + c : 2u * (uint32_t)(n0 + r - BM) * (uint32_t)K + c;
+  }
+  const int nk = K / RK;
+  constexpr int STAGE = ROWS * RK * 2;  // bytes
+  int wr = 0, rd = 0;  // ring positions (byte offsets) of the next stage requested and the next read
+  auto issue = [&](int kt) {
+    bf16* dst = (bf16*)((char*)lds + wr) + wave * 512;
+    wr = wr == (S - 1) * STAGE ? 0 : wr + STAGE;
+#pragma unroll
+    for (int u = 0; u < LPW; ++u)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(32 * u < BM ? ra : rb, (lds_ptr_t)(dst + 2048 * u), 16, (int)off[u],
+                                               kt * (2 * RK), 0, 0);
+  };
+  const int wm = (wave % CW) % CWM, wn = (wave % CW) / CWM;
+  floatx16 acc[NI][MI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < MI; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  struct Frags {
+    bf16x8 a[4][MI], b[4][NI];
+  };
+  int fo[4];  // byte offsets of the lane's fragments of a stage, per 16-wide k sub-step
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) fo[ks] = l32 * 128 + (((2 * ks + hi) ^ ((l32 >> 1) & 7)) << 4);
+  const int wa = wm * MI * 4096, wb = BM * 128 + wn * NI * 4096;
+  auto fread = [&](Frags& f) {
+    const int base = rd;
+    rd = rd == (S - 1) * STAGE ? 0 : rd + STAGE;
+    const char* sa = (const char*)lds + (base + wa);
+    const char* sb = (const char*)lds + (base + wb);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+      for (int j = 0; j < MI; ++j) f.a[ks][j] = *reinterpret_cast<const bf16x8*>(sa + fo[ks] + j * 4096);
+#pragma unroll
+      for (int i = 0; i < NI; ++i) f.b[ks][i] = *reinterpret_cast<const bf16x8*>(sb + fo[ks] + i * 4096);
+    }
+  };
+  auto mfma = [&](const Frags& f) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < MI; ++j) {
+          if (epi_lnfold(EPI))
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, f.b[ks][i]),
+                                                               __builtin_bit_cast(f16x8, f.a[ks][j]), acc[i][j], 0, 0, 0);
+          else
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[ks][i], f.a[ks][j], acc[i][j], 0, 0, 0);
+        }
+  };
+  // a stage's MFMAs, the next stage's fragment reads between the first half of
+  // them (so that they have landed by the barrier) and D loads between the others
+  auto pace = [&](auto D_) {
+    constexpr int ND = decltype(D_)::value, NM = 4 * MI * NI, NR = 4 * (MI + NI), H = NM / 2;
+#pragma unroll
+    for (int g = 0; g < NM; ++g) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (g < H) __builtin_amdgcn_sched_group_barrier(0x100, NR / H, 0);
+      else if (ND) __builtin_amdgcn_sched_group_barrier(0x020, (ND + NM - H - 1) / (NM - H), 0);
+    }
+  };
+  auto next = [&](Frags& cur, Frags& nxt) {
+    fread(nxt);
+    mfma(cur);
+    pace(std::integral_constant<int, 0>{});
+  };
+  const int pre = min(S, nk);
+  for (int s = 0; s < pre; ++s) issue(s);
+  // stage 0: the loads of stages 1 .. pre - 1 may stay in flight
+  if (pre == S) RingWait<(S - 1) * LPW>::go();
+  else if (pre == S / 2) RingWait<(S / 2 - 1) * LPW>::go();
+  else RingWait<0>::go();
+  Frags f0, f1;  // stage kt's fragments are in f0 when nk - kt is even
+  if (nk & 1) fread(f1);
+  else fread(f0);
+  int kt = 0;
+  auto steady = [&](Frags& cur, Frags& nxt) {
+    RingWait<(S - 2) * LPW>::go();  // stage kt + 1 landed, stage kt's fragments read by every wave
+    fread(nxt);
+    issue(kt + S);
+    mfma(cur);
+    pace(std::integral_constant<int, LPW>{});
+    ++kt;
+  };
+  if (nk > S && (nk & 1)) steady(f1, f0);
+  while (kt + S < nk) {
+    steady(f0, f1);
+    steady(f1, f0);
+  }
+  // the last S stages: nothing left to request
+  ring_tail<S>([&](auto I_) {
+    constexpr int I = decltype(I_)::value;  // S - I stages left, this one included
+    if (S - I > nk) return;
+    RingWait<(I < S - 1 ? S - 2 - I : 0) * LPW>::go();
+    Frags& cur = (S - I) & 1 ? f1 : f0;
+    Frags& nxt = (S - I) & 1 ? f0 : f1;
+    if (I < S - 1) next(cur, nxt);
+    else mfma(cur);
+  });
+  if (wave >= CW) return;
+#pragma unroll
+  for (int j = 0; j < MI; ++j) {
+    const int m = m0 + (wm * MI + j) * 32 + l32;
+    if (m >= M) continue;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) store_acc<EPI>(acc[i][j], m, n0 + (wn * NI + i) * 32 + 4 * hi, bias, R, ldr, C, ldc, ln);
+  }
+}
 
 constexpr int kGroupM = 8;  // row blocks that share each column block in turn (L2 reuse)
 
@@ -652,14 +748,45 @@ static hipError_t plain(const void* A, int lda, const void* Bt, const float* bia
   return hipGetLastError();
 }
 
-// Shapes the persistent kernel takes without splitting rows: N a multiple of
-// the tile, K of two k steps and at least four, M at least 2048 rows (below,
-// the launch covers too few of the CUs), element offsets within int32.
+// Shapes the persistent kernel takes: N a multiple of the tile, K of two k
+// steps and at least four, M at least 2048 rows (below, its launch covers too
+// few of the CUs), element offsets within int32.
 static bool persistent_shape(int M, int N, int K, long long ld_max) {
   return N % PT == 0 && K % (2 * PK) == 0 && K >= 4 * PK && M >= 2048 && (long long)M * ld_max < (1ll << 31) &&
          (long long)N * K < (1ll << 31);
 }
-bool gemm_ln_ok(int N, int K, int lda, int ldc) { return N % GN == 0 && K % GK == 0 && lda % 8 == 0 && ldc % 8 == 0; }
+
+// Tile choice of the bf16 MFMA products: the least estimated time, from the
+// measured cost of each tile's round over the CUs (us: a fixed part, prologue
+// and epilogue, and a part per 64 columns of k) and the rate at which the L2s
+// deliver operands to all CUs (about 16 MB per us). Small tiles spread a small
+// M over more CUs, large ones read less per flop. On the MI355X the estimate
+// is within 20% of the measured time for M from 34 to 18000 at (N, K) of the
+// 512- and 1024-wide models' projections, and picks a tile within 15% of the
+// fastest. kPersistent is the 256x256 kernel.
+struct TileCost {
+  int bm, bn;
+  double fix, step;
+};
+enum { T32x32, T32x64, T64x64, T64x128, T128x128, kPersistent, kTiles };
+static const TileCost kTileCost[kTiles] = {{32, 32, 2.0, 0.092},  {32, 64, 2.0, 0.115},   {64, 64, 2.2, 0.15},
+                                           {64, 128, 4.3, 0.21}, {128, 128, 7.0, 0.28}, {PT, PT, 10.0, 1.0}};
+static int pick_tile(int M, int N, int K, bool persistent, int n_cu) {
+  int best = T128x128;
+  double best_us = 1e30;
+  for (int c = 0; c < kTiles; ++c) {
+    if (c == kPersistent && !persistent) continue;
+    const TileCost& t = kTileCost[c];
+    const double tiles = (double)((M + t.bm - 1) / t.bm) * (N / t.bn);
+    const double rounds = (double)(((long long)tiles + n_cu - 1) / n_cu);
+    const double compute = rounds * (t.fix + t.step * (K / RK));
+    const double l2 = t.fix + tiles * (t.bm + t.bn) * 2.0 * K / 16e6;
+    const double us = std::max(compute, l2);
+    if (us < best_us) best_us = us, best = c;
+  }
+  return best;
+}
+bool gemm_ln_ok(int N, int K, int lda, int ldc) { return N % 128 == 0 && K % RK == 0 && lda % 8 == 0 && ldc % 8 == 0; }
 
 hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const float* bias, const void* R, int ldr,
                        void* C, int ldc, int M, int N, int K, Epilogue epi, hipStream_t s, LnResid ln) {
@@ -690,54 +817,52 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
                        (((uintptr_t)Bt & 15) == 0) && (((uintptr_t)C & 15) == 0) && (((uintptr_t)R & 15) == 0) &&
                        (((uintptr_t)bias & 15) == 0) && (((uintptr_t)ln.g & 15) == 0) &&
                        (((uintptr_t)ln.b & 15) == 0);
-  if (N % GN != 0 || K % GK != 0 || !aligned)
+  if (N % 128 != 0 || K % RK != 0 || !aligned)
     return plain<bf16>(A, lda, Bt, bias, R, ldr, C, ldc, M, N, K, epi, ln, s);
   const bf16* a = (const bf16*)A;
   const bf16* b = (const bf16*)Bt;
-  // Persistent kernel: K a multiple of 128 and at least 256 (its load stream
-  // runs three k steps ahead), element offsets within int32.
-  if (persistent_shape(M, N, K, std::max({(long long)lda, (long long)ldc, (long long)ldr}))) {
-    // the current device's CU count, looked up once per device
-    static std::atomic<int> cu_of_device[64];
-    int dev = 0, n_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
-    if (dev >= 0) n_cu = cu_of_device[dev].load(std::memory_order_relaxed);
-    if (n_cu <= 0) {
-      if (dev < 0 || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-          n_cu < 8)
-        n_cu = 256;
-      if (dev >= 0) cu_of_device[dev].store(n_cu, std::memory_order_relaxed);
-    }
-    const int tiles_n = N / PT, tiles_m = (M + PT - 1) / PT, n_tiles = tiles_n * tiles_m;
-    const int per_xcd = (n_tiles + 7) / 8;
-    const int grid = 8 * std::max(1, std::min(n_cu / 8, per_xcd));
+  // the current device's CU count, looked up once per device
+  static std::atomic<int> cu_of_device[64];
+  int dev = 0, n_cu = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
+  if (dev >= 0) n_cu = cu_of_device[dev].load(std::memory_order_relaxed);
+  if (n_cu <= 0) {
+    if (dev < 0 || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 8)
+      n_cu = 256;
+    if (dev >= 0) cu_of_device[dev].store(n_cu, std::memory_order_relaxed);
+  }
+  const bool persistent = persistent_shape(M, N, K, std::max({(long long)lda, (long long)ldc, (long long)ldr}));
+  const int tile = pick_tile(M, N, K, persistent, n_cu);
+  const int tiles_n = N / kTileCost[tile].bn, tiles_m = (M + kTileCost[tile].bm - 1) / kTileCost[tile].bm;
+  const int n_tiles = tiles_n * tiles_m, per_xcd = (n_tiles + 7) / 8;
 #define TX_GP4(E)                                                                                               \
-  gemm_bf16_p4<E><<<grid, 256, 0, s>>>(a, lda, b, bias, R, ldr, C, ldc, M, N, K, tiles_m, tiles_n, n_tiles, \
-                                       per_xcd, ln)
-    switch (epi) {
-      case EPI_BIAS: TX_GP4(EPI_BIAS); break;
-      case EPI_BIAS_GELU: TX_GP4(EPI_BIAS_GELU); break;
-      case EPI_BIAS_RESID: TX_GP4(EPI_BIAS_RESID); break;
-      case EPI_BIAS_RESLN: TX_GP4(EPI_BIAS_RESLN); break;
-      case EPI_LN: TX_GP4(EPI_LN); break;
-      case EPI_LN_GELU: TX_GP4(EPI_LN_GELU); break;
-    }
-#undef TX_GP4
-    return hipGetLastError();
+  gemm_bf16_p4<E><<<8 * std::max(1, std::min(n_cu / 8, per_xcd)), 256, 0, s>>>(a, lda, b, bias, R, ldr, C, ldc, M, N, \
+                                                                              K, tiles_m, tiles_n, n_tiles, per_xcd, ln)
+  // tiles in column order when the weight is the larger operand (each XCD then
+  // reads a part of it), in row order otherwise
+#define TX_GR(E, BM, BN, MI, NI, S)                                                                                  \
+  gemm_bf16_ring<E, BM, BN, MI, NI, S><<<8 * per_xcd, 256, 0, s>>>(a, lda, b, bias, R, ldr, C, ldc, M, N, K, tiles_m, \
+                                                                   tiles_n, M <= N, ln)
+#define TX_GT(E)                                          \
+  switch (tile) {                                         \
+    case T32x32: TX_GR(E, 32, 32, 1, 1, 16); break;       \
+    case T32x64: TX_GR(E, 32, 64, 1, 1, 6); break;        \
+    case T64x64: TX_GR(E, 64, 64, 1, 1, 4); break;        \
+    case T64x128: TX_GR(E, 64, 128, 1, 2, 6); break;      \
+    case T128x128: TX_GR(E, 128, 128, 2, 2, 4); break;    \
+    default: TX_GP4(E); break;                            \
   }
-  const int tiles_n = N / GN, tiles_m = (M + GM - 1) / GM, n_tiles = tiles_n * tiles_m;
-  const int grid = ((n_tiles + 7) / 8) * 8;
-#define TX_G128(E) \
-  gemm_bf16_mfma<E><<<grid, 256, 0, s>>>(a, lda, b, bias, R, ldr, C, ldc, M, N, K, tiles_n, n_tiles, ln)
   switch (epi) {
-    case EPI_BIAS: TX_G128(EPI_BIAS); break;
-    case EPI_BIAS_GELU: TX_G128(EPI_BIAS_GELU); break;
-    case EPI_BIAS_RESID: TX_G128(EPI_BIAS_RESID); break;
-    case EPI_BIAS_RESLN: TX_G128(EPI_BIAS_RESLN); break;
-    case EPI_LN: TX_G128(EPI_LN); break;
-    case EPI_LN_GELU: TX_G128(EPI_LN_GELU); break;
+    case EPI_BIAS: TX_GT(EPI_BIAS); break;
+    case EPI_BIAS_GELU: TX_GT(EPI_BIAS_GELU); break;
+    case EPI_BIAS_RESID: TX_GT(EPI_BIAS_RESID); break;
+    case EPI_BIAS_RESLN: TX_GT(EPI_BIAS_RESLN); break;
+    case EPI_LN: TX_GT(EPI_LN); break;
+    case EPI_LN_GELU: TX_GT(EPI_LN_GELU); break;
   }
-#undef TX_G128
+#undef TX_GT
+#undef TX_GR
+#undef TX_GP4
   return hipGetLastError();
 }
 

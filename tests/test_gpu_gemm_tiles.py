@@ -1,0 +1,41 @@
+"""The projection kernels at the edges of their tiles: one request scored with
+its first C candidates, C on both sides of every tile height (32, 64, 128 rows
+and the persistent kernel's 256) and at one row, for models whose projections
+have 2, 3, 4, 8 and 32 k steps (the ring of stages shorter than its depth, odd,
+and longer). Every tile sums an output in the same order, so each score equals,
+bitwise, the one of the whole candidate set; that one is checked against the
+oracle within the bf16 bar."""
+import numpy as np
+import pytest
+
+from paper_2607_28940_amd import inputs as I
+from paper_2607_28940_amd.inputs import ModelConfig
+from tests.parity_util import BF16_TOL, DeviceCase, check_err, log, oracle_request, score_err
+
+pytestmark = pytest.mark.gpu
+
+MODELS = {"k2": ModelConfig(128, 2, 256, 1, 1, rel_pos_buckets=16),
+          "k3": ModelConfig(192, 3, 256, 1, 2, rel_pos_buckets=16),
+          "k4-k6": ModelConfig(256, 2, 384, 1, 2, rel_pos_buckets=16),
+          "k8-k32": ModelConfig(512, 8, 2048, 1, 2, rel_pos_buckets=16)}
+
+
+@pytest.mark.parametrize("name", MODELS)
+def test_score_independent_of_tile(oracle_mod, name):
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    torch.cuda.set_device(0)
+    model = MODELS[name]
+    wl = I.custom_workload(model, cfg_id=81, L=[70], S=[3], C=[2600])
+    w = I.make_weights(model, ("sharp", "affine"))
+    run = DeviceCase(wl, w)
+    run.build([0])
+    Xc = I.request_tokens(wl, 0, I.STREAM_CANDIDATES)
+    base = run.score([0], cand=[Xc])[0]
+    assert np.all(np.isfinite(base))
+    for C in (1, 28, 29, 30, 60, 61, 62, 125, 126, 253, 254, 600, 1300, 2100):
+        assert np.array_equal(run.score([0], cand=[Xc[:C]])[0], base[:C]), C
+    n = 300
+    err = score_err(base[:n], oracle_request(oracle_mod.Oracle(model, w), wl, 0, cand=Xc[:n])[0])
+    log(f"gemm tiles {name}: max err {err['max']:.3e} p99 {err['p99']:.3e}")
+    check_err(err, BF16_TOL)
