@@ -50,20 +50,6 @@ struct MfmaAcc {
 // raw logit goes through `mask(key, s)`, which returns it (plus any bias, in
 // raw units) or -inf; other tiles skip that work. The O^T rescale is skipped when no lane's
 // max moved.
-// LDS addresses of the MFMA fragments. Padded tiles: K rows of KLD elements,
-// V^T rows of VLD. Swizzled tiles (SWZ, filled by direct-to-LDS loads): K
-// rows of DH elements with 16-byte slot s of row r holding chunk s ^ (r mod
-// DH/8), V^T rows of 64 with slot s holding chunk s ^ ((r / 2) mod 8); both
-// keep the fragment reads of 8 consecutive rows on distinct banks.
-template <int DH, int KLD, bool SWZ>
-__device__ __forceinline__ int k_frag(int row, int slot) {
-  return SWZ ? row * DH + ((slot ^ (row & (DH / 8 - 1))) << 3) : row * KLD + (slot << 3);
-}
-template <int VLD, bool SWZ>
-__device__ __forceinline__ int v_frag(int row, int slot) {
-  return SWZ ? row * 64 + ((slot ^ ((row >> 1) & 7)) << 3) : row * VLD + (slot << 3);
-}
-
 // The tile arithmetic takes its operands from fragment sources:
 // kfrag(kb, kk) is K row kb * 32 + l32, features 16 kk + 8 hi .. + 7;
 // vfrag(ks, db) is V^T row 32 db + l32, stored columns
@@ -80,11 +66,14 @@ __device__ __forceinline__ void pace_lds_reads() {
   __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
 }
 
-// First half: S^T = K Q^T, the online softmax update and P^T in bf16.
-template <int DH, bool FROM_LDS, class KFrag, class Mask>
-__device__ __forceinline__ void mfma_qk_softmax(KFrag kfrag, const bf16x8 (&qf)[DH / 16], MfmaAcc<DH>& acc,
-                                                float scale_log2, int hi, bool masked, Mask mask, bf16x8 (&pf)[4],
-                                                float thr = -1.f) {
+// First half: S^T = K Q^T, the online softmax update and P^T in bf16. fix(s)
+// masks the raw logits and adds what differs per key; with SHIFT, `shift` (raw
+// units) belongs to every logit of the tile and joins the offset of the
+// exponentials instead of costing an addition per logit.
+template <int DH, bool FROM_LDS, bool SHIFT, class KFrag, class Fix>
+__device__ __forceinline__ void mfma_qk_softmax_fix(KFrag kfrag, const bf16x8 (&qf)[DH / 16], MfmaAcc<DH>& acc,
+                                                    float scale_log2, Fix fix, float shift, bf16x8 (&pf)[4],
+                                                    float thr) {
   floatx16 s[2];
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
@@ -94,18 +83,14 @@ __device__ __forceinline__ void mfma_qk_softmax(KFrag kfrag, const bf16x8 (&qf)[
     for (int kk = 0; kk < DH / 16; ++kk) s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag(kb, kk), qf[kk], s[kb], 0, 0, 0);
   }
   if (FROM_LDS) pace_lds_reads<DH / 8>();
-  if (masked) {  // wave-uniform
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) s[kb][v] = mask(kb * 32 + 8 * (v >> 2) + 4 * hi + (v & 3), s[kb][v]);
-  }
+  fix(s);
   float mx = -INFINITY;
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
     for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[kb][v]);
   mx = xor32_max(mx);
+  if (SHIFT) mx += shift;
   // Lazy reference max: probabilities are exp2((s - m) * scale) against a
   // reference m that only moves when this tile would push one above 2^8
   // (fine for fp32 sums and bf16 P); O and l are rescaled only then. The
@@ -123,7 +108,7 @@ __device__ __forceinline__ void mfma_qk_softmax(KFrag kfrag, const bf16x8 (&qf)[
       for (int v = 0; v < 16; ++v) acc.o[db][v] *= alpha;
     acc.m = m_new;
   }
-  const float off = (acc.m == -INFINITY) ? 0.f : -acc.m * scale_log2;
+  const float off = (acc.m == -INFINITY) ? 0.f : (SHIFT ? shift - acc.m : -acc.m) * scale_log2;
   float rs = 0.f;
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb)
@@ -139,6 +124,22 @@ __device__ __forceinline__ void mfma_qk_softmax(KFrag kfrag, const bf16x8 (&qf)[
   for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
     for (int t = 0; t < 8; ++t) pf[ks][t] = (bf16)s[ks >> 1][8 * (ks & 1) + t];
+}
+
+// The same with a mask per logit (`masked` uniform across the wave).
+template <int DH, bool FROM_LDS, class KFrag, class Mask>
+__device__ __forceinline__ void mfma_qk_softmax(KFrag kfrag, const bf16x8 (&qf)[DH / 16], MfmaAcc<DH>& acc,
+                                                float scale_log2, int hi, bool masked, Mask mask, bf16x8 (&pf)[4],
+                                                float thr = -1.f) {
+  auto fix = [&](floatx16(&s)[2]) {
+    if (masked) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[kb][v] = mask(kb * 32 + 8 * (v >> 2) + 4 * hi + (v & 3), s[kb][v]);
+    }
+  };
+  mfma_qk_softmax_fix<DH, FROM_LDS, false>(kfrag, qf, acc, scale_log2, fix, 0.f, pf, thr);
 }
 
 // Second half: O^T += V^T P^T. From LDS the V^T fragment reads run four ahead
@@ -161,17 +162,18 @@ __device__ __forceinline__ void mfma_attend_frags(KFrag kfrag, VFrag vfrag, cons
   mfma_pv<DH, FROM_LDS>(vfrag, pf, acc);
 }
 
-// The same tile with K and V^T staged in LDS.
-template <int DH, int KLD, int VLD, class Mask, bool SWZ = false>
+// The same tile with K and V^T staged in LDS: K rows of KLD elements, V^T rows
+// of VLD (padded, so that fragment reads of neighbouring rows use other banks).
+template <int DH, int KLD, int VLD, class Mask>
 __device__ __forceinline__ void mfma_attend_tile(const bf16* __restrict__ sK, const bf16* __restrict__ sV,
                                                  const bf16x8 (&qf)[DH / 16], MfmaAcc<DH>& acc, float scale_log2,
                                                  int l32, int hi, bool masked, Mask mask) {
   auto kfrag = [&](int kb, int kk) {
-    return *reinterpret_cast<const bf16x8*>(&sK[k_frag<DH, KLD, SWZ>(kb * 32 + l32, 2 * kk + hi)]);
+    return *reinterpret_cast<const bf16x8*>(&sK[(kb * 32 + l32) * KLD + ((2 * kk + hi) << 3)]);
   };
   auto vfrag = [&](int ks, int db) {
     const int kbase = (ks >> 1) * 32 + 16 * (ks & 1) + 8 * hi;  // in the V^T tile's permuted key order
-    return *reinterpret_cast<const bf16x8*>(&sV[v_frag<VLD, SWZ>(32 * db + l32, kbase >> 3)]);
+    return *reinterpret_cast<const bf16x8*>(&sV[(32 * db + l32) * VLD + kbase]);
   };
   mfma_attend_frags<DH, true>(kfrag, vfrag, qf, acc, scale_log2, hi, masked, mask);
 }
@@ -243,17 +245,16 @@ struct PageDma {
 };
 
 // ============================================================================
-// bf16 paged attention on MFMA.
+// bf16 paged attention on MFMA: the page loop of a block.
 //
 // A block of 4 waves serves up to 128 queries of one (request, head); each
 // wave owns 32 queries. For every 64-token page the block stages K [64][dh]
-// and V^T [dh][64] in LDS (double-buffered: the next page travels from HBM/L2
-// straight into LDS with buffer loads to LDS while the current one is used, no
-// register staging), so every K/V byte fetched from HBM/L2 feeds all queries
-// of the block. The page keeps V^T in the column order the PV MFMA wants; the
-// tiles are XOR-swizzled in LDS (the swizzle applied on the global side, since
-// each lane's 16 bytes land at a fixed slot) so fragment reads are
-// bank-conflict free without padding.
+// and V^T [dh][64] in LDS straight from HBM/L2 (buffer loads to LDS, no register
+// staging), so every K/V byte fetched feeds all queries of the block. The page
+// keeps V^T in the column order the PV MFMA wants; the tiles are XOR-swizzled
+// in LDS (the swizzle applied on the global side, since each lane's 16 bytes
+// land at a fixed slot) so fragment reads are bank-conflict free without
+// padding.
 //
 // Per wave and page:  S^T = K Q^T  (v_mfma_f32_32x32x16_bf16, keys as rows so
 // that a lane holds 32 keys of one query: the softmax row reduction is within
@@ -261,37 +262,136 @@ struct PageDma {
 // O^T += V^T P^T with P^T taken straight from the S^T accumulators (the MFMA
 // k index is permuted consistently on both operands, so no register shuffle
 // is needed; V^T supplies the matching keys with one 16-byte LDS read).
-// Keys past the request's length are masked by selection and their V columns
-// are zeroed in LDS so that unused page slots (of any content) never reach
-// the output.
+// What bounds it is each wave's dependent page chain (QK on MFMA, softmax on
+// the VALU, PV on MFMA), so K is double-buffered and V^T single-buffered
+// (3 x 64 x DH elements): at d_h = 128 three blocks share a CU, i.e. three
+// waves a SIMD overlap their chains. Page p + 1's K is requested at the top of
+// page p's body, page p + 1's V^T once page p's PV has left the buffer; before
+// the PV each wave waits for its own V^T loads only (the K loads issued after
+// them may stay in flight) and the block meets at a barrier.
+//
+// active(p) (uniform in the wave): whether the wave has work on page p of the
+// range; qk(p, kfrag, pf): its scores and probabilities (mfma_qk_softmax).
+// Every body ends on a barrier and the last requests nothing, so sKV is free
+// after the loop. Keys past the request's length on its last page are masked
+// by qk; the cache keeps zeros in their V^T columns (the page scatter writes
+// them), so their zero probabilities never meet other values. With a last_valid
+// below 64 the columns of the last page's keys from last_valid on are zeroed
+// in LDS (a prefix of the cached tokens: the page holds later tokens there).
 // ============================================================================
-template <int DH, bool CAUSAL>
-__global__ __launch_bounds__(256, 2) void paged_attn_mfma(const bf16* __restrict__ q, int ldq, bf16* __restrict__ out,
-                                                           int ldo, const bf16* __restrict__ pool,
-                                                           const int32_t* __restrict__ page_table, int max_pages,
-                                                           PageGeom g, int layer_slot, const AttnReq* __restrict__ reqs,
-                                                           const AttnTile* __restrict__ tiles,
-                                                           const float* __restrict__ rel, int R, float scale_log2) {
-  constexpr int KLD = DH, VLD = 64;  // swizzled, unpadded tiles
-  // K page buffers 0, 1, then V^T page buffers 0, 1
-  __shared__ __attribute__((aligned(16))) bf16 sKV[4 * 64 * DH];
+template <int DH, class Active, class QK>
+__device__ __forceinline__ void page_loop(bf16* sKV, const bf16* __restrict__ pool, const int32_t* __restrict__ ptab,
+                                          int n_pages, const PageGeom& g, int layer_slot, int h, int wave, int lane,
+                                          MfmaAcc<DH>& acc, Active active, QK qk, int last_valid = kPage) {
+  const int l32 = lane & 31, hi = lane >> 5;
+  // K page buffers 0, 1, then the V^T page buffer
   bf16* const sK0 = sKV;
-  bf16* const sK1 = sKV + 64 * DH;
-  bf16* const sV0 = sKV + 2 * 64 * DH;
+  bf16* const sV = sKV + 2 * 64 * DH;
+  const PageDma<DH> pd(wave, lane);
+  // page-table window: lane l holds the pool index of page wbase + l of the
+  // range; a page's index is read from its lane into a scalar, so the page
+  // loads take a uniform address and no memory read of their own
+  int wbase = 0;
+  int pwin = ptab[min(lane, n_pages - 1)];
+  auto page = [&](int p) { return pool + (size_t)__builtin_amdgcn_readlane(pwin, p - wbase) * g.page_elems; };
+  pd.load(page(0) + g.k_off(layer_slot, h), pd.koff, sK0);
+  pd.load(page(0) + g.v_off(layer_slot, h), pd.voff, sV);
+  // LDS byte offsets of the lane's MFMA fragments under the swizzles of
+  // PageDma: K row kb * 32 + l32, slot 2 kk + hi at
+  // kb * 64 DH * 2 + (kxor ^ 32 kk); V^T row 32 db + l32, slot 2 ks + hi at
+  // db * 4096 + (vxor ^ 32 ks). One register each; every read costs one XOR.
+  const int kxor = (l32 * DH * 2) | ((hi ^ (l32 & (DH / 8 - 1))) << 4);
+  const int vxor = (l32 * 128) | ((hi ^ ((l32 >> 1) & 7)) << 4);
+  const char* const lds = reinterpret_cast<const char*>(sKV);
+  __syncthreads();
+  for (int p = 0; p < n_pages; ++p) {
+    const int b = (p & 1) * (64 * DH);
+    if (p + 1 < n_pages) pd.load(page(p + 1) + g.k_off(layer_slot, h), pd.koff, sK0 + (64 * DH - b));
+    const bool work = active(p);
+    bf16x8 pf[4];
+    // the K buffer's offset joins the base before the XORs (it lies above
+    // their bits); the opaque copies keep the per-read addresses from being
+    // hoisted out of the loop into registers held across it
+    int kx = kxor + 2 * b, vx = vxor + 2 * 2 * 64 * DH;
+    asm volatile("" : "+v"(kx), "+v"(vx));
+    if (work) {
+      auto kfrag = [&](int kb, int kk) {
+        return *reinterpret_cast<const bf16x8*>(lds + (kx ^ (32 * kk)) + kb * 64 * DH);
+      };
+      qk(p, kfrag, pf);
+    }
+    if (p > 0) {
+      // V^T of page p (requested after page p - 1's PV) in LDS for every wave;
+      // the DH / 32 K loads of page p + 1 issued since may stay in flight
+      if (p + 1 < n_pages) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(DH / 32) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+    if (last_valid < kPage && p + 1 == n_pages) {
+      for (int e = wave * 64 + lane; e < DH * 64; e += 256) {
+        const int r = e >> 6, col = e & 63;
+        const int chunk = (col >> 3) ^ ((r >> 1) & 7);  // stored chunk held at this slot
+        if (vt_col(chunk * 8 + (col & 7)) >= last_valid) sV[e] = (bf16)0.f;
+      }
+      __syncthreads();
+    }
+    if (work) {
+      auto vfrag = [&](int ks, int db) {
+        return *reinterpret_cast<const bf16x8*>(lds + (vx ^ (32 * ks)) + db * 4096);
+      };
+      mfma_pv<DH, true>(vfrag, pf, acc);
+    }
+    __syncthreads();  // K and V^T of page p no longer read; K of page p + 1 landed
+    // no load is in flight here: the window moves when the next body's K
+    // load (page p + 2) would leave it
+    if (p + 2 - wbase >= 64 && p + 2 < n_pages) {
+      wbase = p + 1;
+      pwin = ptab[min(p + 1 + lane, n_pages - 1)];
+      // consumed here, where it is the only load in flight (so that no later
+      // read of the window waits on the page loads issued after it)
+      asm volatile("" : "+v"(pwin));
+    }
+    if (p + 1 < n_pages) pd.load(page(p + 1) + g.v_off(layer_slot, h), pd.voff, sV);
+  }
+}
+
+// ============================================================================
+// Encoder self-attention (causal, relative-position bias) and, without the
+// mask, the decoder cross-attention at d_h = 64, over tiles of 128 queries.
+//
+// The bias of a (query, key) pair depends on their distance only and is
+// constant from R - 1 on, so a wave meets three kinds of pages: far ones
+// (every distance at least R - 1: one constant, which joins the exponentials'
+// offset), near ones (the bias added per logit, no mask) and the last one or
+// two (bias and causal mask); pages past the wave's last query are skipped.
+// The bias comes from LDS (TABLE): srel[j] holds the bias of distance
+// kRelC - j, kRelC = R + 96, in raw logit units for every distance a near page
+// can show, so that a lane's 32 keys are 32 constant offsets from one address
+// (consecutive words over the lanes: no bank conflicts). Against a gather from
+// memory, clamp and compare per logit on every page (and two page buffers of
+// V^T, two blocks per CU): 1170 -> 455 us per layer for 32 users of 500-6000
+// tokens (66.5 k in all) at d_h = 128, 19.5 -> 9.3 us for 3 users of 90-400 at 64.
+// Tables past kCausalMaxRel buckets do not fit beside the pages and are read
+// from memory.
+// ============================================================================
+constexpr int kCausalMaxRel = 1024;
+template <int DH, bool CAUSAL, bool TABLE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 4 : 3, DH == 64 ? 4 : 3))) void
+paged_attn_mfma(const bf16* __restrict__ q, int ldq, bf16* __restrict__ out, int ldo, const bf16* __restrict__ pool,
+                const int32_t* __restrict__ page_table, int max_pages, PageGeom g, int layer_slot,
+                const AttnReq* __restrict__ reqs, const AttnTile* __restrict__ tiles, const float* __restrict__ rel,
+                int R, float scale_log2, float bump_thr) {
+  __shared__ __attribute__((aligned(16))) bf16 sKV[3 * 64 * DH];
+  extern __shared__ float srel[];  // TABLE: R + 192 entries
 
   const AttnTile tile = tiles[blockIdx.x];
   if (tile.q_count <= 0) return;
   const AttnReq rq = reqs[tile.req];
   const int h = tile.head;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
-
-  const int qi = wave * 32 + l32;
   const bool wave_active = wave * 32 < tile.q_count;
-  const int i = tile.q_begin + min(qi, tile.q_count - 1);
+  const int i = tile.q_begin + min(wave * 32 + l32, tile.q_count - 1);
   const int row = i < rq.qa_n ? rq.qa_row + i : rq.qb_row + (i - rq.qa_n);
-  const int qpos = rq.pos0 + i;
-  const float bias_scale = kLog2e / scale_log2;  // logit bias expressed in raw q.k units
 
   // Q as the MFMA B operand: lane holds Q[query l32][16*kk + 8*hi .. +8]
   bf16x8 qf[DH / 16];
@@ -300,101 +400,75 @@ __global__ __launch_bounds__(256, 2) void paged_attn_mfma(const bf16* __restrict
 #pragma unroll
     for (int kk = 0; kk < DH / 16; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qr + 16 * kk);
   }
-
   MfmaAcc<DH> acc;
   acc.init();
 
   const int kv_len = rq.kv_len;
   int n_pages = (kv_len + kPage - 1) / kPage;
-  if (CAUSAL) {
-    const int last_pos = rq.pos0 + tile.q_begin + tile.q_count - 1;
-    n_pages = min(n_pages, last_pos / kPage + 1);
-  }
+  if (CAUSAL) n_pages = min(n_pages, (rq.pos0 + tile.q_begin + tile.q_count - 1) / kPage + 1);
   const int32_t* ptab = page_table + (size_t)rq.slot * max_pages;
-
-  // Pages travel HBM/L2 -> LDS with buffer_load_dwordx4 ... lds: each wave
-  // moves DH/32 KB of the K slab and as much of the V^T slab per page; lane l
-  // of a 1 KB load fills 16-byte slot l of it with the chunk the swizzle puts
-  // there. Page p+1 is requested while page p is used; every wave waits for
-  // its own loads before the page's closing barrier.
-  const PageDma<DH> pd(wave, lane);
-  auto dma = [&](int p, bf16* dK, bf16* dV) {
-    const bf16* base = pool + (size_t)ptab[p] * g.page_elems;
-    pd.load(base + g.k_off(layer_slot, h), pd.koff, dK);
-    pd.load(base + g.v_off(layer_slot, h), pd.voff, dV);
-  };
-  // keys past the request's length on its last page: V^T columns zeroed in LDS
-  // (the page may hold anything there; their K logits are masked anyway)
-  auto zero_tail = [&](int p, bf16* dV) {
-    const int valid = kv_len - p * kPage;
-    for (int e = tid; e < DH * 64; e += 256) {
-      const int r = e >> 6, col = e & 63;
-      const int chunk = (col >> 3) ^ ((r >> 1) & 7);  // stored chunk held at this slot
-      if (vt_col(chunk * 8 + (col & 7)) >= valid) dV[e] = (bf16)0.f;
-    }
-  };
-  const bool partial = kv_len % kPage != 0;
-  dma(0, sK0, sV0);
-  __syncthreads();
-  if (n_pages == 1 && partial) {
-    zero_tail(0, sV0);
-    __syncthreads();
+  const float bias_scale = kLog2e / scale_log2;  // logit bias in raw q.k units
+  const int kRelC = R + 96, last = max(R - 1, 0);
+  float far_bias = 0.f;
+  if (CAUSAL && R > 0) {
+    if (TABLE)
+      for (int j = tid; j < R + 192; j += 256) srel[j] = rel[h * R + min(max(kRelC - j, 0), last)] * bias_scale;
+    far_bias = rel[h * R + last] * bias_scale;
   }
-  auto step = [&](int p, const bf16* cK, const bf16* cV, bf16* nK, bf16* nV) {
-    if (p + 1 < n_pages) dma(p + 1, nK, nV);
-    if (wave_active) {
-      const int key0 = p * kPage;
-      // masking is needed on the request's last (partial) page and, when
-      // causal, on pages that reach past this wave's first query position;
-      // the relative-position bias applies to every causal tile
-      const bool needs_mask = CAUSAL || key0 + kPage > kv_len;
-      auto mask = [&](int kl, float x) {
-        const int key = key0 + kl;
-        bool ok = key < kv_len;
-        if (CAUSAL) {
-          ok = ok && key <= qpos;
-          if (R > 0) x += rel[h * R + min(max(qpos - key, 0), R - 1)] * bias_scale;
-        }
-        return ok ? x : -INFINITY;
-      };
-      mfma_attend_tile<DH, KLD, VLD, decltype(mask), true>(cK, cV, qf, acc, scale_log2, l32, hi, needs_mask, mask);
+  const int wq0 = rq.pos0 + tile.q_begin + wave * 32;  // the wave's first and last query positions
+  const int wq1 = rq.pos0 + tile.q_begin + min(wave * 32 + 31, tile.q_count - 1);
+  const int qpos = rq.pos0 + i;
+  auto active = [&](int p) { return wave_active && (!CAUSAL || p * kPage <= wq1); };
+  auto qk = [&](int p, auto kfrag, bf16x8(&pf)[4]) {
+    const int key0 = p * kPage;
+    if (!CAUSAL) {
+      mfma_qk_softmax<DH, true>(kfrag, qf, acc, scale_log2, hi, key0 + kPage > kv_len, [&](int kl, float x) {
+        return key0 + kl < kv_len ? x : -INFINITY;
+      }, pf, bump_thr);
+      return;
     }
-    __syncthreads();  // page p+1 in LDS for every wave; page p no longer read
-    if (p + 2 == n_pages && partial) {
-      zero_tail(p + 1, nV);
-      __syncthreads();
-    }
+    const bool far = key0 + kPage - 1 + last <= wq0;
+    auto fix = [&](floatx16(&s)[2]) {
+      if (far) return;
+      if (R > 0) {
+        // near pages hold distances up to R + 92 and, past the diagonal, down to -94
+        const int d0 = qpos - key0 - 4 * hi;
+        const float* u = srel + (kRelC - d0);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const int kl = kb * 32 + 8 * (v >> 2) + (v & 3);
+            s[kb][v] += TABLE ? u[kl] : rel[h * R + min(max(d0 - kl, 0), last)] * bias_scale;
+          }
+      }
+      if (key0 + kPage - 1 > wq0) {  // on the diagonal (where also the cache's unused slots are)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            s[kb][v] = key0 + kb * 32 + 8 * (v >> 2) + 4 * hi + (v & 3) <= qpos ? s[kb][v] : -INFINITY;
+      }
+    };
+    mfma_qk_softmax_fix<DH, true, true>(kfrag, qf, acc, scale_log2, fix, far ? far_bias : 0.f, pf, bump_thr);
   };
-  // one loop body for both buffers (the buffer offset is uniform), so the
-  // fragment addresses are not held twice
-  for (int p = 0; p < n_pages; ++p) {
-    const int b = (p & 1) * (64 * DH);
-    step(p, sK0 + b, sV0 + b, sK0 + (64 * DH - b), sV0 + (64 * DH - b));
-  }
-  // every step ends on a barrier, so no page buffer is read any more: waves
-  // 0-1 park their output rows in sK0, waves 2-3 in sK1
-  mfma_store_out_staged<DH>(acc, (wave < 2 ? sK0 : sK1) + (wave & 1) * 32 * DH, out, ldo, h * DH, lane,
-                            tile.q_begin + wave * 32, tile.q_count - wave * 32, rq.qa_n, rq.qa_row, rq.qb_row);
+  page_loop<DH>(sKV, pool, ptab, n_pages, g, layer_slot, h, wave, lane, acc, active, qk,
+                !CAUSAL && kv_len % kPage ? kv_len % kPage : kPage);
+  // the page buffers are free: waves 0-1 park their output rows in K buffer 0,
+  // waves 2-3 in K buffer 1
+  mfma_store_out_staged<DH>(acc, sKV + wave * 32 * DH, out, ldo, h * DH, lane, tile.q_begin + wave * 32,
+                            tile.q_count - wave * 32, rq.qa_n, rq.qa_row, rq.qb_row);
 }
 
 // ============================================================================
-// The decoder cross-attention (no causal mask, d_h = 128) with three blocks per
-// CU, i.e. three waves per SIMD to overlap each wave's dependent page chain
-// (QK on MFMA, softmax on the VALU, PV on MFMA) with two others instead of
-// one: 48 KB of LDS (K double-buffered, V^T single-buffered) and at most 168
-// registers. Page p + 1's K is requested at the top of page p's body, page
-// p + 1's V^T once page p's PV has left the buffer; before the PV each wave
-// waits for its own V^T loads only (the K loads issued after them may stay in
-// flight) and the block meets at a barrier. Same arithmetic in the same order
-// as paged_attn_mfma.
+// The decoder cross-attention at d_h = 128 (no causal mask), at most 168
+// registers, so that three blocks share a CU.
 // The tiles come as one list per XCD (XCD x: tiles[xoff[x] .. xoff[x + 1])).
 // A tile (XTile) covers up to 128 queries of one request and head against the
 // key pages page_begin .. page_end - 1: all of the request's pages (its rows
 // are written normalised), or one part of them (a kv-split tile: the
 // unnormalised output, reference max and running sum go to a partial slot,
-// combined later by xattn_merge). Keys past the request's length on its last
-// page are masked; the cache keeps zeros in their V^T columns (the page
-// scatter writes them), so their zero probabilities never meet other values.
+// combined later by xattn_merge).
 // ============================================================================
 template <int DH, bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void paged_attn_mfma3(
@@ -402,11 +476,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const int32_t* __restrict__ page_table, int max_pages, PageGeom g, int layer_slot,
     const XTile* __restrict__ tiles, const int32_t* __restrict__ xoff, float* __restrict__ partial,
     float scale_log2, float bump_thr) {
-  // K page buffers 0, 1, then the V^T page buffer
   __shared__ __attribute__((aligned(16))) bf16 sKV[3 * 64 * DH];
-  bf16* const sK0 = sKV;
-  bf16* const sK1 = sKV + 64 * DH;
-  bf16* const sV = sKV + 2 * 64 * DH;
 
   // block b runs on XCD b % 8 and takes entry b / 8 of that XCD's tile list
   const int t_idx = xoff[blockIdx.x & 7] + (int)(blockIdx.x >> 3);
@@ -429,68 +499,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   MfmaAcc<DH> acc;
   acc.init();
 
-  const int kv_len = tile.kv_len;
-  const int p0 = tile.page_begin, n_pages = tile.page_end - tile.page_begin;
+  const int kv_len = tile.kv_len, p0 = tile.page_begin;
   const int32_t* ptab = page_table + (size_t)tile.slot * max_pages + p0;
-  const PageDma<DH> pd(wave, lane);
-  // page-table window: lane l holds the pool index of page wbase + l of the
-  // range; a page's index is read from its lane into a scalar, so the page
-  // loads take a uniform address and no memory read of their own
-  int wbase = 0;
-  int pwin = ptab[min(lane, n_pages - 1)];
-  auto page = [&](int p) { return pool + (size_t)__builtin_amdgcn_readlane(pwin, p - wbase) * g.page_elems; };
-  pd.load(page(0) + g.k_off(layer_slot, h), pd.koff, sK0);
-  pd.load(page(0) + g.v_off(layer_slot, h), pd.voff, sV);
-  // LDS byte offsets of the lane's MFMA fragments, the swizzles of k_frag
-  // and v_frag in closed form: K row kb * 32 + l32, slot 2 kk + hi at
-  // kb * 64 DH * 2 + (kxor ^ 32 kk); V^T row 32 db + l32, slot 2 ks + hi at
-  // db * 4096 + (vxor ^ 32 ks). One register each; every read costs one XOR.
-  const int kxor = (l32 * DH * 2) | ((hi ^ (l32 & (DH / 8 - 1))) << 4);
-  const int vxor = (l32 * 128) | ((hi ^ ((l32 >> 1) & 7)) << 4);
-  const char* const lds = reinterpret_cast<const char*>(sKV);
-  __syncthreads();
-  for (int p = 0; p < n_pages; ++p) {
-    const int b = (p & 1) * (64 * DH);
-    if (p + 1 < n_pages) pd.load(page(p + 1) + g.k_off(layer_slot, h), pd.koff, sK0 + (64 * DH - b));
+  auto qk = [&](int p, auto kfrag, bf16x8(&pf)[4]) {
     const int key0 = (p0 + p) * kPage;
-    bf16x8 pf[4];
-    // the K buffer's offset joins the base before the XORs (it lies above
-    // their bits); the opaque copies keep the per-read addresses from being
-    // hoisted out of the loop into registers held across it
-    int kx = kxor + 2 * b, vx = vxor + 2 * 2 * 64 * DH;
-    asm volatile("" : "+v"(kx), "+v"(vx));
-    if (wave_active) {
-      auto kfrag = [&](int kb, int kk) {
-        return *reinterpret_cast<const bf16x8*>(lds + (kx ^ (32 * kk)) + kb * 64 * DH);
-      };
-      mfma_qk_softmax<DH, true>(kfrag, qf, acc, scale_log2, hi, key0 + kPage > kv_len, [&](int kl, float x) {
-        return key0 + kl < kv_len ? x : -INFINITY;
-      }, pf, bump_thr);
-    }
-    if (p > 0) {
-      // V^T of page p (requested after page p - 1's PV) in LDS for every wave;
-      // the DH / 32 K loads of page p + 1 issued since may stay in flight
-      if (p + 1 < n_pages) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(DH / 32) : "memory");
-      else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    }
-    if (wave_active) {
-      auto vfrag = [&](int ks, int db) {
-        return *reinterpret_cast<const bf16x8*>(lds + (vx ^ (32 * ks)) + db * 4096);
-      };
-      mfma_pv<DH, true>(vfrag, pf, acc);
-    }
-    __syncthreads();  // K and V^T of page p no longer read; K of page p + 1 landed
-    // no load is in flight here: the window moves when the next body's K
-    // load (page p + 2) would leave it
-    if (p + 2 - wbase >= 64 && p + 2 < n_pages) {
-      wbase = p + 1;
-      pwin = ptab[min(p + 1 + lane, n_pages - 1)];
-      // consumed here, where it is the only load in flight (so that no later
-      // read of the window waits on the page loads issued after it)
-      asm volatile("" : "+v"(pwin));
-    }
-    if (p + 1 < n_pages) pd.load(page(p + 1) + g.v_off(layer_slot, h), pd.voff, sV);
-  }
+    mfma_qk_softmax<DH, true>(kfrag, qf, acc, scale_log2, hi, key0 + kPage > kv_len, [&](int kl, float x) {
+      return key0 + kl < kv_len ? x : -INFINITY;
+    }, pf, bump_thr);
+  };
+  page_loop<DH>(sKV, pool, ptab, tile.page_end - p0, g, layer_slot, h, wave, lane, acc,
+                [&](int) { return wave_active; }, qk);
   if (SPLIT) {
     // kv-split tile: fp32 O (unnormalised, features 32 db + 8 gq + 4 hi ..),
     // reference max and running sum of each of the wave's queries
@@ -511,10 +529,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     }
     return;
   }
-  // every body ends on a barrier and the last requests nothing: waves 0-1
-  // park their output rows in K buffer 0, waves 2-3 in K buffer 1
-  mfma_store_out_staged<DH>(acc, (wave < 2 ? sK0 : sK1) + (wave & 1) * 32 * DH, out, ldo, h * DH, lane,
-                            tile.q_begin + wave * 32, tile.q_count - wave * 32, tile.qa_n, tile.qa_row, tile.qb_row);
+  // the page buffers are free: waves 0-1 park their output rows in K buffer 0,
+  // waves 2-3 in K buffer 1
+  mfma_store_out_staged<DH>(acc, sKV + wave * 32 * DH, out, ldo, h * DH, lane, tile.q_begin + wave * 32,
+                            tile.q_count - wave * 32, tile.qa_n, tile.qa_row, tile.qb_row);
 }
 
 // ============================================================================
@@ -1002,14 +1020,19 @@ hipError_t launch_paged_attention(bool bf, const void* q, int ldq, void* out, in
     const bf16* qq = (const bf16*)q;
     bf16* oo = (bf16*)out;
     const bf16* pp = (const bf16*)pool;
-#define TX_PA(DH, CZ)                                                                                              \
-  paged_attn_mfma<DH, CZ><<<n_tiles, 256, 0, s>>>(qq, ldq, oo, ldo, pp, page_table, max_pages, g, layer_slot, reqs, \
-                                                   tiles, rel, R, sl2)
+    const bool table = R <= kCausalMaxRel;
+    const size_t rel_bytes = causal && table && R > 0 ? (size_t)(R + 192) * sizeof(float) : 0;
+#define TX_PA(DH, CZ, TZ)                                                                                             \
+  paged_attn_mfma<DH, CZ, TZ><<<n_tiles, 256, rel_bytes, s>>>(qq, ldq, oo, ldo, pp, page_table, max_pages, g,        \
+                                                              layer_slot, reqs, tiles, rel, R, sl2, 8.f / sl2)
     if (g.dh == 64) {
-      if (causal) TX_PA(64, true); else TX_PA(64, false);
+      if (causal && table) TX_PA(64, true, true);
+      else if (causal) TX_PA(64, true, false);
+      else TX_PA(64, false, false);
     } else {
-      if (causal) TX_PA(128, true);
-      else TX_PA(128, false);
+      if (causal && table) TX_PA(128, true, true);
+      else if (causal) TX_PA(128, true, false);
+      else return hipErrorInvalidValue;  // the cross-attention's own tile lists (launch_cross_attention)
     }
 #undef TX_PA
     return hipGetLastError();
