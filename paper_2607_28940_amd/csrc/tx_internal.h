@@ -228,11 +228,12 @@ hipError_t launch_lg_attention(bool bf, const void* q, int ldq, void* out, int l
                                const AttnReq* reqs, const AttnTile* tiles, int n_tiles, int q_block, int l_local,
                                const void* gkv, int gkv_ld, int dec_layer, hipStream_t s);
 // Decoder cross-attention over per-XCD tile lists (bf16, d_h = 128): XCD x
-// owns tiles[xoff[x] .. xoff[x + 1]); block b (which the hardware runs on XCD
-// b % 8) takes entry b / 8 of its XCD's list, on a grid of 8 x longest_list
-// blocks. The whole-request tiles write their rows; the kv-split tiles, a
-// tile set and a launch of their own, write partial slots (kXPartBytes
-// each), which the merge items then combine into the output rows.
+// owns tiles[xoff[x] .. xoff[x + 1]) and the kv-split tiles likewise; block b
+// (which the hardware runs on XCD b % 8) takes entry b / 8 of its XCD's
+// kv-split tiles, then of its whole-request tiles, on a grid of 8 x (longest
+// list of each) blocks. The whole-request tiles write their rows; the
+// kv-split tiles write partial slots (kXPartBytes each), which the merge items
+// then combine into the output rows.
 bool cross_attention_split_ok(bool bf, int dh);
 constexpr int kXQueryBlock = 128;  // queries per tile
 constexpr int kXBlocksPerCu = 3;   // resident blocks per CU

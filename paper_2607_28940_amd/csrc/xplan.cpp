@@ -13,44 +13,58 @@ namespace tx {
 // are (request, head, 128-query block) against all the request's pages. When
 // the batch leaves the GPU's resident blocks short of work, long units are
 // split by pages (kv-split): a unit of P pages takes ceil(P / Q) parts of at
-// least kXMinSplitPages, Q = the per-block share of all pages when every
-// resident block has about two units; the parts' partial results are merged
-// afterwards. Columns (request, head, part) group the query blocks that read
+// least kXMinSplitPages, Q = the resident blocks' equal share of all pages
+// (tiles run longest first, so the makespan needs no finer parts: half that
+// share split a ragged batch's longest units for no gain and a merge of 11 us
+// per layer); the parts' partial results are merged afterwards. Columns (request, head, part) group the query blocks that read
 // the same pages; columns go to XCDs longest first (each XCD's least loaded
 // first), and each XCD's list keeps a column's tiles adjacent, so that the
 // resident blocks of one XCD read a page slab from its L2 close in time.
-// Whole-request and kv-split columns form two tile sets, balanced apart.
+// Whole-request and kv-split columns form two tile sets, balanced together
+// (one launch runs both).
 void xattn_plan(const std::vector<AttnReq>& reqs, int H, int resident_blocks, int max_parts, XPlan& out) {
   struct Unit {
     int req, head, q0, qn, pages;
   };
   std::vector<Unit> units;
   int64_t work = 0;
+  int longest = 0;  // pages of the longest unit
   for (int r = 0; r < (int)reqs.size(); ++r) {
     const int nq = reqs[r].qa_n + reqs[r].qb_n;
     const int pages = (reqs[r].kv_len + kPage - 1) / kPage;
     if (nq <= 0 || pages <= 0) continue;
+    longest = std::max(longest, pages);
     for (int h = 0; h < H; ++h)
       for (int q0 = 0; q0 < nq; q0 += kXQueryBlock) {
         units.push_back({r, h, q0, std::min(kXQueryBlock, nq - q0), pages});
         work += pages;
       }
   }
-  // page quantum: raised until the partial slots suffice
-  int64_t quantum = std::max<int64_t>(kXMinSplitPages, (work + 2 * resident_blocks - 1) / (2 * resident_blocks));
+  int64_t quantum = std::max<int64_t>(kXMinSplitPages, (work + resident_blocks - 1) / resident_blocks);
   auto parts_of = [&](int pages) -> int {
     if (pages <= quantum) return 1;
     return (int)std::max<int64_t>(1, std::min<int64_t>((pages + quantum - 1) / quantum, pages / kXMinSplitPages));
   };
-  for (;;) {
+  // page quantum: raised to the smallest one for which the partial slots
+  // suffice (fewer parts the larger it is; past the longest unit there are none)
+  auto slots = [&](int64_t qm) {
+    quantum = qm;
     int64_t n = 0;
-    for (const Unit& u : units) {
-      const int k = parts_of(u.pages);
-      if (k > 1) n += k;
+    for (const AttnReq& rq : reqs) {
+      const int nq = rq.qa_n + rq.qb_n, pages = (rq.kv_len + kPage - 1) / kPage;
+      if (nq <= 0 || pages <= 0) continue;
+      const int k = parts_of(pages);
+      if (k > 1) n += (int64_t)k * H * ((nq + kXQueryBlock - 1) / kXQueryBlock);
     }
-    if (n <= max_parts) break;
-    quantum *= 2;
+    return n;
+  };
+  int64_t lo = quantum, hi = std::max<int64_t>(quantum, longest);
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) / 2;
+    if (slots(mid) <= max_parts) hi = mid;
+    else lo = mid + 1;
   }
+  quantum = lo;
   // columns: (request, head, part) with their query blocks
   struct Column {
     int64_t cost;
@@ -81,13 +95,13 @@ void xattn_plan(const std::vector<AttnReq>& reqs, int H, int resident_blocks, in
   out.n_parts = next_part;
   std::stable_sort(cols.begin(), cols.end(), [](const Column& a, const Column& b) { return a.cost > b.cost; });
   std::vector<XTile> lists[2][8];
-  int64_t load[2][8] = {};
+  int64_t load[8] = {};
   for (const Column& c : cols) {
     const int kind = c.n_parts > 1;
     int x = 0;
     for (int k = 1; k < 8; ++k)
-      if (load[kind][k] < load[kind][x]) x = k;
-    load[kind][x] += c.cost;
+      if (load[k] < load[x]) x = k;
+    load[x] += c.cost;
     for (int u = c.first; u < c.first + c.count; ++u) {
       const Unit& un = units[u];
       const AttnReq& rq = reqs[un.req];

@@ -10,7 +10,7 @@ namespace tx {
 
 // One tile set per kind: whole-request tiles (rows written normalised) and
 // kv-split tiles (partial slots, merged afterwards); each is a per-XCD list
-// set of its own, balanced on its own, for a launch of its own.
+// set of its own, the XCDs' loads balanced over both.
 struct XTileSet {
   std::vector<XTile> tiles;   // per-XCD lists, concatenated
   std::vector<int32_t> xoff;  // 9 entries: XCD x owns tiles[xoff[x] .. xoff[x + 1])
@@ -26,8 +26,13 @@ struct XPlan {
   int n_parts = 0;  // partial slots used (kv-split tiles)
 };
 
-// Fewest pages a kv-split part covers.
-constexpr int kXMinSplitPages = 16;
+// Fewest pages a kv-split part covers. A part costs a partial slot written and
+// read back (66 KB each way), a page of its block about 1 us; with 4 pages
+// instead of 16 (and the whole-request tiles in the same launch) a layer of 8
+// users of 500-4000 tokens went from 36 + 31 + 11 us (whole, split, merge) to
+// 29 + 7, of one user of 16384 (64-page parts before, 37 now) from 97 + 19 to
+// 79 + 8.
+constexpr int kXMinSplitPages = 4;
 
 // Tiles for the requests of one cross-attention launch (queries of request r:
 // reqs[r].qa_n + reqs[r].qb_n, keys: its first kv_len cached tokens) on a GPU
