@@ -913,7 +913,9 @@ __global__ __launch_bounds__(256, 2) void self_attn_mfma(const bf16* __restrict_
 // ============================================================================
 // Plain paged attention (fp32 models, head widths without an MFMA variant).
 // 64 queries per block, 4 lanes per query, each lane owning dh/4 features;
-// pages staged in LDS; keys processed one at a time with the online softmax.
+// pages staged in LDS; eight keys per step of the online softmax, so that
+// their dot products overlap and the running state is updated once per step
+// (24 queries, 256 keys at d_h = 32: 67 us with one key at a time, 43 now).
 // ============================================================================
 template <typename T, int DH>
 __global__ __launch_bounds__(256) void paged_attn_plain(const T* __restrict__ q, int ldq, T* __restrict__ out, int ldo,
@@ -922,9 +924,11 @@ __global__ __launch_bounds__(256) void paged_attn_plain(const T* __restrict__ q,
                                                         const AttnReq* __restrict__ reqs,
                                                         const AttnTile* __restrict__ tiles, bool causal,
                                                         const float* __restrict__ rel, int R, float scale_log2) {
-  constexpr int DP = DH / 4;
-  __shared__ float sK[kPage][DH + 1];
-  __shared__ float sV[DH][kPage + 1];
+  constexpr int DP = DH / 4, NK = 8;
+  static_assert(kPage % NK == 0, "a step stays within the page's rows in LDS");
+  // rows of whole 16-byte units, so that a lane reads 4 features (K) or 4 keys (V) at once
+  __shared__ __attribute__((aligned(16))) float sK[kPage][DH + 4];
+  __shared__ __attribute__((aligned(16))) float sV[DH][kPage + 4];
   const AttnTile tile = tiles[blockIdx.x];
   if (tile.q_count <= 0) return;
   const AttnReq rq = reqs[tile.req];
@@ -952,28 +956,49 @@ __global__ __launch_bounds__(256) void paged_attn_plain(const T* __restrict__ q,
     const T* vp = pool + base + g.v_off(layer_slot, h);
     const int valid = min(kPage, kv_len - p * kPage);
     for (int e = tid; e < kPage * DH; e += 256) {
-      sK[e / DH][e % DH] = (float)kp[e];
+      sK[e / DH][e % DH] = e / DH < valid ? (float)kp[e] : 0.f;
       const int vr = e / kPage, key = vt_col(e % kPage);
       sV[vr][key] = key < valid ? (float)vp[e] : 0.f;
     }
     __syncthreads();
     if (active) {
-      for (int j = 0; j < valid; ++j) {
-        const int key = p * kPage + j;
-        if (causal && key > qpos) break;
-        float s = 0.f;
+      const int jn = causal ? min(valid, qpos - p * kPage + 1) : valid;  // keys this query sees on the page
+      for (int j0 = 0; j0 < jn; j0 += NK) {
+        float sc[NK], mx = -INFINITY;
 #pragma unroll
-        for (int e = 0; e < DP; ++e) s = fmaf(qv[e], sK[j][part * DP + e], s);
-        s = quad_sum(s);  // the query's four lanes
-        s *= scale_log2;
-        if (causal && R > 0) s += rel[h * R + min(qpos - key, R - 1)] * kLog2e;
-        const float m_new = fmaxf(m_run, s);
+        for (int u = 0; u < NK; ++u) {
+          float x = 0.f;
+#pragma unroll
+          for (int e = 0; e < DP; e += 4) {
+            const floatx4 k4 = *reinterpret_cast<const floatx4*>(&sK[j0 + u][part * DP + e]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) x = fmaf(qv[e + t], k4[t], x);
+          }
+          x = quad_sum(x) * scale_log2;  // the query's four lanes
+          if (causal && R > 0) x += rel[h * R + min(max(qpos - (p * kPage + j0 + u), 0), R - 1)] * kLog2e;
+          sc[u] = j0 + u < jn ? x : -INFINITY;
+          mx = fmaxf(mx, sc[u]);
+        }
+        const float m_new = fmaxf(m_run, mx);  // finite: key j0 is visible
         const float alpha = exp2f(m_run - m_new);
-        const float pj = exp2f(s - m_new);
-        l_run = l_run * alpha + pj;
-#pragma unroll
-        for (int e = 0; e < DP; ++e) acc[e] = fmaf(pj, sV[part * DP + e][j], acc[e] * alpha);
         m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int u = 0; u < NK; ++u) {
+          sc[u] = exp2f(sc[u] - m_new);
+          l_run += sc[u];
+        }
+#pragma unroll
+        for (int e = 0; e < DP; ++e) {
+          float x = acc[e] * alpha;
+#pragma unroll
+          for (int u = 0; u < NK; u += 4) {
+            const floatx4 v4 = *reinterpret_cast<const floatx4*>(&sV[part * DP + e][j0 + u]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) x = fmaf(sc[u + t], v4[t], x);
+          }
+          acc[e] = x;
+        }
       }
     }
     __syncthreads();
