@@ -18,6 +18,7 @@
 
 #include "tx_internal.h"
 #include "xplan.h"
+#include "meta_put.h"
 
 using namespace tx;
 
@@ -701,17 +702,23 @@ int tx_profile_read(double* total_ms, int64_t* launches, double* flops, double* 
 // ------------------------------------------------------------------ planning
 namespace {
 
-// Host-side metadata of one pass, uploaded in one copy to the workspace head.
+// Host-side metadata of one pass, uploaded in one piece to the workspace head.
 struct Meta {
   std::vector<char> buf;
   template <class T>
   size_t put(const std::vector<T>& v) {
-    const size_t o = align_up(buf.size());
+    const size_t o = align_up(buf.size(), 64);
     buf.resize(o + std::max<size_t>(v.size(), 1) * sizeof(T), 0);
     if (!v.empty()) memcpy(buf.data() + o, v.data(), v.size() * sizeof(T));
     return o;
   }
 };
+
+// A small upload travels as a kernel's arguments (one launch, no staging
+// buffer or event to keep); larger ones are copied from the staging.
+hipError_t upload(Stager& stager, void* dst, const void* src, size_t bytes, hipStream_t st, bool may_grow = true) {
+  return bytes <= sizeof(MetaArg) ? put_meta(dst, src, bytes, st) : stager.upload(dst, src, bytes, st, may_grow);
+}
 
 // kv-split of the pipelined cross-attention: partial slots per pass (each
 // kXPartBytes of workspace).
@@ -962,7 +969,7 @@ int run_encoder_pass(tx_kv_cache* c, const char* X, int64_t rows, const std::vec
   const size_t o_chunks = meta.put(chunks), o_preqs = meta.put(preqs), o_ptiles = meta.put(ptiles);
   const size_t mb = meta_bound(n, rows, mx, m->H);
   if (meta.buf.size() > mb) return fail(TX_E_NOMEM, "internal: metadata %zu > bound %zu", meta.buf.size(), mb);
-  TX_HIP(c->st.upload(ws, meta.buf.data(), meta.buf.size(), st));
+  TX_HIP(upload(c->st, ws, meta.buf.data(), meta.buf.size(), st));
   const ScatterTile* d_ptiles = (const ScatterTile*)(ws + o_ptiles);
   const int n_ptiles = (int)ptiles.size();
   const AttnReq* d_areq = (const AttnReq*)(ws + o_areq);
@@ -1126,7 +1133,7 @@ int kv_cache_build(tx_kv_cache* c, int32_t n, const int32_t* ids, const void* X,
   // from here on a failure leaves these requests without a cache, holding
   // their pages until release
   int rc = TX_OK;
-  const hipError_t e = c->st.upload(c->d_table, c->h_table.data(), c->h_table.size() * 4, st);
+  const hipError_t e = upload(c->st, c->d_table, c->h_table.data(), c->h_table.size() * 4, st);
   if (e != hipSuccess) rc = fail(TX_E_HIP, "page table upload failed: %s", hipGetErrorString(e));
   if (rc == TX_OK) rc = encode_call(c, TX_OP_BUILD, n, ids, X, off, ws, ws_bytes, st);
   for (int i = 0; i < n; ++i) c->len[ids[i]] = rc == TX_OK ? off[i + 1] - off[i] : -1;
@@ -1167,7 +1174,7 @@ int kv_cache_append(tx_kv_cache* c, int32_t n, const int32_t* ids, const void* X
   // from here on a failure leaves these requests without a cache, holding
   // their pages until release
   int rc = TX_OK;
-  const hipError_t e = c->st.upload(c->d_table, c->h_table.data(), c->h_table.size() * 4, st);
+  const hipError_t e = upload(c->st, c->d_table, c->h_table.data(), c->h_table.size() * 4, st);
   if (e != hipSuccess) rc = fail(TX_E_HIP, "page table upload failed: %s", hipGetErrorString(e));
   if (rc == TX_OK) rc = encode_call(c, TX_OP_APPEND, n, ids, X, off, ws, ws_bytes, st);
   for (int i = 0; i < n; ++i) c->len[ids[i]] = rc == TX_OK ? c->len[ids[i]] + off[i + 1] - off[i] : -1;
@@ -1240,7 +1247,7 @@ int run_score_pass(const tx_kv_cache* c, const int32_t* ids, const int64_t* kvle
   const XDev xd_full = put_plan(x_full), xd_cand = put_plan(x_cand);
   const size_t mb = meta_bound(n, M64, mx, H);
   if (meta.buf.size() > mb) return fail(TX_E_NOMEM, "internal: metadata %zu > bound %zu", meta.buf.size(), mb);
-  TX_HIP(c->st.upload(ws, meta.buf.data(), meta.buf.size(), st, !fixed_staging));
+  TX_HIP(upload(c->st, ws, meta.buf.data(), meta.buf.size(), st, !fixed_staging));
   Carver cv(ws + mb);
   char* T = cv.take<char*>(M64 * d * es);
   char* QKV = cv.take<char*>(M64 * 3 * d * es);
@@ -1253,16 +1260,12 @@ int run_score_pass(const tx_kv_cache* c, const int32_t* ids, const int64_t* kvle
   char* Hf = cv.take<char*>(M64 * F * es);
   float* xpart = xpipe ? cv.take<float*>(kXMaxParts * kXPartBytes) : nullptr;
   // The first layer reads the serving and candidate tokens where they are
-  // (its QKV GEMM and the self-attention output GEMM's residual run once per
-  // token array) when the bf16 GEMMs can take them (16-byte aligned rows) and
-  // both arrays fill the GPU on their own (8192 rows or more: 32 row tiles
-  // of the persistent GEMM); otherwise they are copied into T, where the
-  // later layers' input lives.
+  // (its QKV GEMM and the self-attention output GEMM's residual take rows of
+  // two arrays) when their rows are 16-byte aligned; otherwise they are copied
+  // into T, where the later layers' input lives.
   const char* Xs = xs + (size_t)so[a] * d * es;
   const char* Xc = xc + (size_t)co[a] * d * es;
-  const bool direct = (Ms == 0 || Ms >= 8192) && Mc >= 8192 &&
-                      (!bf || ((Ms == 0 || (uintptr_t)Xs % 16 == 0) && (uintptr_t)Xc % 16 == 0 &&
-                               ((size_t)d * es) % 16 == 0));
+  const bool direct = (Ms == 0 || (uintptr_t)Xs % 16 == 0) && (uintptr_t)Xc % 16 == 0 && ((size_t)d * es) % 16 == 0;
   if (!direct)
     TX_LAUNCH(K_COPY, 0, 2.0 * M64 * d * es, [&]() -> hipError_t {
       if (Ms) {
@@ -1320,15 +1323,18 @@ int run_score_pass(const tx_kv_cache* c, const int32_t* ids, const int64_t* kvle
     const bool fold_in = l > 0 && fold_qkv, fold_out = !last && fold_qkv;
     // layer input rows r0 .. M - 1: T, or the token arrays in place (first layer)
     const bool in_place = l == 0 && direct;
+    auto two_arrays = [&](const void* a2, const void* r2) {
+      LnResid x;
+      if (Ms) x.a2 = a2, x.r2 = r2, x.m1 = (int)Ms;
+      return x;
+    };
     TX_LAUNCH(K_GEMM_QKV, q.first, q.second, [&]() -> hipError_t {
       if (fold_in)
         return launch_gemm(bf, Ys[(k0 - 1) & 1], d, L.qkvf.w, L.qkvf.b, nullptr, 0, QKV, 3 * d, M, 3 * d, d, EPI_LN,
                            st, LnResid{Ss[(k0 - 1) & 1], L.qkvf.cs, nullptr});
       if (!in_place) return launch_gemm(bf, T, d, L.qkv.w, L.qkv.b, nullptr, 0, QKV, 3 * d, M, 3 * d, d, EPI_BIAS, st);
-      hipError_t e = launch_gemm(bf, Xs, d, L.qkv.w, L.qkv.b, nullptr, 0, QKV, 3 * d, (int)Ms, 3 * d, d, EPI_BIAS, st);
-      if (e != hipSuccess) return e;
-      return launch_gemm(bf, Xc, d, L.qkv.w, L.qkv.b, nullptr, 0, QKV + (size_t)Ms * 3 * d * es, 3 * d, (int)Mc,
-                         3 * d, d, EPI_BIAS, st);
+      return launch_gemm(bf, Ms ? Xs : Xc, d, L.qkv.w, L.qkv.b, nullptr, 0, QKV, 3 * d, M, 3 * d, d, EPI_BIAS, st,
+                         two_arrays(Xc, nullptr));
     }());
     TX_LAUNCH(K_SELF_ATTN, 4 * dd * (last ? self_cand : self_full), esd * (3 * Md * dd + Mrd * dd),
               launch_self_attention(bf, QKV, d, H, A, (const SelfReq*)(ws + o_sreq), stl, n_st, last, st));
@@ -1340,12 +1346,10 @@ int run_score_pass(const tx_kv_cache* c, const int32_t* ids, const int64_t* kvle
                            LnResid{Sk(k0 - 1), m->dec[l - 1].ln3g, m->dec[l - 1].ln3b});
       if (!in_place)
         return launch_gemm(bf, A + ro, d, L.o.w, L.o.b, T + ro, d, Yk(k0), d, Mr, d, d, EPI_BIAS_RESID, st);
-      const size_t cs = (size_t)Ms * d * es;  // candidate rows start here in A and Y
-      if (r0 == 0) {
-        hipError_t e = launch_gemm(bf, A, d, L.o.w, L.o.b, Xs, d, Ys[0], d, (int)Ms, d, d, EPI_BIAS_RESID, st);
-        if (e != hipSuccess) return e;
-      }
-      return launch_gemm(bf, A + cs, d, L.o.w, L.o.b, Xc, d, Ys[0] + cs, d, (int)Mc, d, d, EPI_BIAS_RESID, st);
+      if (last || Ms == 0)  // the candidates' rows only
+        return launch_gemm(bf, A + ro, d, L.o.w, L.o.b, Xc, d, Yk(k0), d, Mr, d, d, EPI_BIAS_RESID, st);
+      return launch_gemm(bf, A, d, L.o.w, L.o.b, Xs, d, Yk(k0), d, M, d, d, EPI_BIAS_RESID, st,
+                         two_arrays(A + (size_t)Ms * d * es, Xc));
     }());
     TX_LAUNCH(K_LAYERNORM, 0, (fold ? 1 : 2) * Mrd * dd * esd,
               launch_layernorm(bf, Yk(k0), fold ? nullptr : T + ro, Sk(k0), L.ln1g, L.ln1b, Mr, d, eps, st));

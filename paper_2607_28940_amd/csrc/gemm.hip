@@ -81,10 +81,11 @@ __device__ __forceinline__ float resid4(const u32x2& raw, int e, LnRow st, float
 }
 
 // Epilogue and stores of one 32x32 accumulator: element v is column
-// nb + 8 (v / 4) + v % 4 of row m (the lane's hi half already in nb).
+// nb + 8 (v / 4) + v % 4 of row m (the lane's hi half already in nb); rrow is
+// the residual's row (the model or the sum type, both 16 bits wide).
 template <int EPI>
 __device__ __forceinline__ void store_acc(const floatx16& acc, int m, int nb, const float* __restrict__ bias,
-                                          const void* __restrict__ R, int ldr, void* __restrict__ C, int ldc,
+                                          const bf16* __restrict__ rrow, void* __restrict__ C, int ldc,
                                           const LnResid& ln) {
   LnRow st{0.f, 0.f};
   if (EPI == EPI_BIAS_RESLN || epi_lnfold(EPI)) st = ln.stats[m];
@@ -104,7 +105,7 @@ __device__ __forceinline__ void store_acc(const floatx16& acc, int m, int nb, co
       }
       *reinterpret_cast<bf16x4*>((bf16*)C + (size_t)m * ldc + n) = o;
     } else if (epi_resid(EPI)) {
-      const u32x2 raw = *reinterpret_cast<const u32x2*>((const bf16*)R + (size_t)m * ldr + n);
+      const u32x2 raw = *reinterpret_cast<const u32x2*>(rrow + n);
       floatx4 g4 = {0.f, 0.f, 0.f, 0.f};
       if (EPI == EPI_BIAS_RESLN) {
         g4 = *reinterpret_cast<const floatx4*>(ln.g + n);
@@ -163,7 +164,8 @@ template <int EPI, int BM, int BN, int MI, int NI, int S>
 __global__ __launch_bounds__(256) void gemm_bf16_ring(const bf16* __restrict__ A, int lda, const bf16* __restrict__ Bt,
                                                       const float* __restrict__ bias, const void* __restrict__ R,
                                                       int ldr, void* __restrict__ C, int ldc, int M, int N, int K,
-                                                      int tiles_m, int tiles_n, bool n_major, LnResid ln) {
+                                                      int tiles_m1, int tiles_m, int tiles_n, bool n_major,
+                                                      LnResid ln) {
   constexpr int ROWS = BM + BN, LPW = ROWS / 32;  // 1 KB loads per wave and stage
   constexpr int CWM = BM / (32 * MI), CW = CWM * (BN / (32 * NI));  // waves that compute
   static_assert(CW >= 1 && CW <= 4 && S >= 4 && S % 2 == 0 && ROWS % 32 == 0, "tile shape");
@@ -174,12 +176,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring(const bf16* __restrict__ A
   const int t = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
   if (t >= n_tiles) return;
   const int mt = n_major ? t % tiles_m : t / tiles_n, nt = n_major ? t / tiles_m : t % tiles_n;
-  const int m0 = mt * BM, n0 = nt * BN;
+  // row tiles from tiles_m1 on lie in the second array (see LnResid::a2)
+  const bool second = mt >= tiles_m1;
+  const int row0 = second ? ln.m1 : 0;                            // output row of the array's row 0
+  const int rows = second ? M - ln.m1 : (ln.a2 ? ln.m1 : M);      // rows of the array
+  const int m0 = (second ? mt - tiles_m1 : mt) * BM, n0 = nt * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
 
-  const __amdgpu_buffer_rsrc_t ra =
-      __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, (int)(2u * (uint32_t)M * (uint32_t)lda), 0x00020000);
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+      second ? (void*)ln.a2 : (void*)A, 0, (int)(2u * (uint32_t)rows * (uint32_t)lda), 0x00020000);
   const __amdgpu_buffer_rsrc_t rb =
       __builtin_amdgcn_make_buffer_rsrc((void*)Bt, 0, (int)(2u * (uint32_t)N * (uint32_t)K), 0x00020000);
   // Load u of a wave fills rows 32 u + 8 wave .. + 7 of the stage (A rows, then
@@ -298,9 +304,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring(const bf16* __restrict__ A
 #pragma unroll
   for (int j = 0; j < MI; ++j) {
     const int m = m0 + (wm * MI + j) * 32 + l32;
-    if (m >= M) continue;
+    if (m >= rows) continue;
+    const bf16* rrow = (const bf16*)(second ? ln.r2 : R) + (size_t)m * ldr;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) store_acc<EPI>(acc[i][j], m, n0 + (wn * NI + i) * 32 + 4 * hi, bias, R, ldr, C, ldc, ln);
+    for (int i = 0; i < NI; ++i)
+      store_acc<EPI>(acc[i][j], row0 + m, n0 + (wn * NI + i) * 32 + 4 * hi, bias, rrow, C, ldc, ln);
   }
 }
 
@@ -664,7 +672,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_p4(const bf16* __restrict__ 
   }
 }
 
-// Plain tiled GEMM for fp32 models and shapes the MFMA tiling does not cover:
+// Plain tiled GEMM for shapes and alignments the MFMA kernels do not cover:
 // 64x64 block tile, K step 16, each thread computes 4x4 outputs in fp32.
 // Sum type (pre-LN sums of the residual epilogues): fp16 beside bf16, fp32
 // beside fp32.
@@ -728,6 +736,101 @@ __global__ __launch_bounds__(256) void gemm_plain(const T* __restrict__ A, int l
       Ct[(size_t)m * ldc + n] = (CT)epilogue<EPI>(acc[i][j], bn, r);
     }
   }
+}
+
+// fp32 models: v_mfma_f32_16x16x4_f32, one wave per TM x TN tiles of 16x16
+// outputs, four waves per block on adjacent column tiles, no LDS. A lane loads
+// 16 bytes of its A and B rows per 16 columns of k; the MFMA of element t sums
+// k = 4 (lane / 16) + t, the same columns on both operands. What bounds the
+// fp32 model's few rows is latency (loads, then 4 MFMAs per 16 columns), which
+// small tiles over many CUs and four chunks in flight keep short: M 24, K 64
+// or 256 9-18 us per launch on gemm_plain (64x64 tiles through LDS, a barrier
+// per 16 columns), 3-6 here. 32x32 outputs per wave once those fill the CUs
+// (half the operand reads); both sum each output in the same order.
+template <int EPI, int TM, int TN>
+__global__ __launch_bounds__(256) void gemm_f32_mfma(const float* __restrict__ A, int lda, const float* __restrict__ Bt,
+                                                     const float* __restrict__ bias, const float* __restrict__ R,
+                                                     int ldr, float* __restrict__ C, int ldc, int M, int N, int K,
+                                                     LnResid ln) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
+  const int m0 = blockIdx.y * (16 * TM), n0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * (16 * TN);
+  if (n0 >= N) return;  // whole waves; the kernel has no barrier
+  const float *ap[TM], *bp[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int m = min(m0 + 16 * i + l16, M - 1);
+    ap[i] = (ln.a2 && m >= ln.m1 ? (const float*)ln.a2 + (size_t)(m - ln.m1) * lda : A + (size_t)m * lda) + 4 * g;
+  }
+#pragma unroll
+  for (int j = 0; j < TN; ++j) bp[j] = Bt + (size_t)min(n0 + 16 * j + l16, N - 1) * K + 4 * g;
+  floatx4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  constexpr int D = 4;  // chunks of 16 columns in flight
+  floatx4 a[D][TM], b[D][TN];
+  auto load = [&](int s, int k0) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) a[s][i] = *reinterpret_cast<const floatx4*>(ap[i] + k0);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) b[s][j] = *reinterpret_cast<const floatx4*>(bp[j] + k0);
+  };
+#pragma unroll
+  for (int s = 0; s < D; ++s)
+    if (16 * s < K) load(s, 16 * s);
+  for (int k0 = 0; k0 < K; k0 += 16 * D)
+#pragma unroll
+    for (int s = 0; s < D; ++s) {
+      if (k0 + 16 * s >= K) break;
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][i][t], b[s][j][t], acc[i][j], 0, 0, 0);
+      if (k0 + 16 * (s + D) < K) load(s, k0 + 16 * (s + D));
+    }
+  // accumulator element v of tile (i, j): row m0 + 16 i + 4 g + v, column n0 + 16 j + l16
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int n = n0 + 16 * j + l16;
+    if (n >= N) continue;
+    float bn = bias[n], gn = 0.f;
+    if (EPI == EPI_BIAS_RESLN) {
+      bn += ln.b[n];
+      gn = ln.g[n];
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int m = m0 + 16 * i + 4 * g + v;
+        if (m >= M) continue;
+        float r = 0.f;
+        if (epi_resid(EPI))
+          r = ln.a2 && m >= ln.m1 ? ((const float*)ln.r2)[(size_t)(m - ln.m1) * ldr + n] : R[(size_t)m * ldr + n];
+        if (EPI == EPI_BIAS_RESLN) r = ln_resid(r, ln.stats[m], gn);
+        C[(size_t)m * ldc + n] = epilogue<EPI>(acc[i][j][v], bn, r);
+      }
+  }
+}
+
+template <int TM, int TN>
+static hipError_t f32_mfma(const float* A, int lda, const float* Bt, const float* bias, const float* R, int ldr, float* C,
+                           int ldc, int M, int N, int K, Epilogue epi, LnResid ln, hipStream_t s) {
+  const dim3 grid((N + 64 * TN - 1) / (64 * TN), (M + 16 * TM - 1) / (16 * TM));
+#define TX_F32(E) gemm_f32_mfma<E, TM, TN><<<grid, 256, 0, s>>>(A, lda, Bt, bias, R, ldr, C, ldc, M, N, K, ln)
+  switch (epi) {
+    case EPI_BIAS: TX_F32(EPI_BIAS); break;
+    case EPI_BIAS_GELU: TX_F32(EPI_BIAS_GELU); break;
+    case EPI_BIAS_RESID: TX_F32(EPI_BIAS_RESID); break;
+    case EPI_BIAS_RESLN: TX_F32(EPI_BIAS_RESLN); break;
+    default: return hipErrorInvalidValue;  // the LayerNorm-folding epilogues are for bf16 models
+  }
+#undef TX_F32
+  return hipGetLastError();
 }
 
 template <typename T>
@@ -794,12 +897,39 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
   if (epi == EPI_BIAS_RESLN && (!ln.stats || !ln.g || !ln.b)) return hipErrorInvalidValue;
   if (epi_resid(epi) && !R) return hipErrorInvalidValue;
   if (epi_lnfold(epi) && (!bf || !ln.stats || !ln.g || !gemm_ln_ok(N, K, lda, ldc))) return hipErrorInvalidValue;
-  if (!bf) return plain<float>(A, lda, Bt, bias, R, ldr, C, ldc, M, N, K, epi, ln, s);
+  // rows of two arrays on a kernel that takes one: a launch for each
+  auto halves = [&]() {
+    LnResid l1 = ln, l2 = ln;
+    l1.a2 = l1.r2 = l2.a2 = l2.r2 = nullptr;
+    l1.m1 = l2.m1 = 0;
+    if (l2.stats) l2.stats += ln.m1;
+    const size_t es = bf ? 2 : 4;
+    const hipError_t e = launch_gemm(bf, A, lda, Bt, bias, R, ldr, C, ldc, ln.m1, N, K, epi, s, l1);
+    if (e != hipSuccess) return e;
+    return launch_gemm(bf, ln.a2, lda, Bt, bias, ln.r2, ldr, (char*)C + (size_t)ln.m1 * ldc * es, ldc, M - ln.m1, N, K,
+                       epi, s, l2);
+  };
+  if (ln.a2 && (ln.m1 < 0 || ln.m1 > M || (epi_resid(epi) && !ln.r2))) return hipErrorInvalidValue;
+  if (!bf) {
+    // 16-byte operand loads: K a multiple of a chunk, rows and bases aligned (a
+    // caller's tokens may be aligned to 4 bytes only). The grid's y extent
+    // limits the rows.
+    if (K % 16 == 0 && lda % 4 == 0 && (((uintptr_t)A | (uintptr_t)Bt | (uintptr_t)ln.a2) & 15) == 0 &&
+        M <= 16 * 65535) {
+      const float *a = (const float*)A, *b = (const float*)Bt, *r = (const float*)R;
+      if ((long long)((M + 31) / 32) * ((N + 31) / 32) >= 1024)  // four waves on each of 256 CUs
+        return f32_mfma<2, 2>(a, lda, b, bias, r, ldr, (float*)C, ldc, M, N, K, epi, ln, s);
+      return f32_mfma<1, 1>(a, lda, b, bias, r, ldr, (float*)C, ldc, M, N, K, epi, ln, s);
+    }
+    if (ln.a2) return halves();
+    return plain<float>(A, lda, Bt, bias, R, ldr, C, ldc, M, N, K, epi, ln, s);
+  }
   // The MFMA kernels address A, R and C with 32-bit byte offsets: a product
   // whose operands span 2^31 elements or more runs as several row chunks.
   {
     const long long ld_max = std::max({(long long)lda, (long long)ldc, epi_resid(epi) ? (long long)ldr : 1ll});
     const long long rows_max = std::max(256ll, ((1ll << 31) - 1) / ld_max / 256 * 256);
+    if (M > rows_max && ln.a2) return halves();
     if (M > rows_max) {
       for (long long m0 = 0; m0 < M; m0 += rows_max) {
         const int mc = (int)std::min(rows_max, (long long)M - m0);
@@ -816,7 +946,8 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
   const bool aligned = (lda % 8 == 0) && (ldc % 8 == 0) && (ldr % 8 == 0) && (((uintptr_t)A & 15) == 0) &&
                        (((uintptr_t)Bt & 15) == 0) && (((uintptr_t)C & 15) == 0) && (((uintptr_t)R & 15) == 0) &&
                        (((uintptr_t)bias & 15) == 0) && (((uintptr_t)ln.g & 15) == 0) &&
-                       (((uintptr_t)ln.b & 15) == 0);
+                       (((uintptr_t)ln.b & 15) == 0) && ((((uintptr_t)ln.a2 | (uintptr_t)ln.r2) & 15) == 0);
+  if (ln.a2 && (N % 128 != 0 || K % RK != 0 || !aligned)) return halves();
   if (N % 128 != 0 || K % RK != 0 || !aligned)
     return plain<bf16>(A, lda, Bt, bias, R, ldr, C, ldc, M, N, K, epi, ln, s);
   const bf16* a = (const bf16*)A;
@@ -833,7 +964,9 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
   }
   const bool persistent = persistent_shape(M, N, K, std::max({(long long)lda, (long long)ldc, (long long)ldr}));
   const int tile = pick_tile(M, N, K, persistent, n_cu);
-  const int tiles_n = N / kTileCost[tile].bn, tiles_m = (M + kTileCost[tile].bm - 1) / kTileCost[tile].bm;
+  if (ln.a2 && tile == kPersistent) return halves();
+  const int bm = kTileCost[tile].bm, tiles_n = N / kTileCost[tile].bn;
+  const int tiles_m1 = ((ln.a2 ? ln.m1 : M) + bm - 1) / bm, tiles_m = tiles_m1 + (ln.a2 ? (M - ln.m1 + bm - 1) / bm : 0);
   const int n_tiles = tiles_n * tiles_m, per_xcd = (n_tiles + 7) / 8;
 #define TX_GP4(E)                                                                                               \
   gemm_bf16_p4<E><<<8 * std::max(1, std::min(n_cu / 8, per_xcd)), 256, 0, s>>>(a, lda, b, bias, R, ldr, C, ldc, M, N, \
@@ -841,8 +974,8 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
   // tiles in column order when the weight is the larger operand (each XCD then
   // reads a part of it), in row order otherwise
 #define TX_GR(E, BM, BN, MI, NI, S)                                                                                  \
-  gemm_bf16_ring<E, BM, BN, MI, NI, S><<<8 * per_xcd, 256, 0, s>>>(a, lda, b, bias, R, ldr, C, ldc, M, N, K, tiles_m, \
-                                                                   tiles_n, M <= N, ln)
+  gemm_bf16_ring<E, BM, BN, MI, NI, S><<<8 * per_xcd, 256, 0, s>>>(a, lda, b, bias, R, ldr, C, ldc, M, N, K, tiles_m1, \
+                                                                   tiles_m, tiles_n, M <= N, ln)
 #define TX_GT(E)                                          \
   switch (tile) {                                         \
     case T32x32: TX_GR(E, 32, 32, 1, 1, 16); break;       \

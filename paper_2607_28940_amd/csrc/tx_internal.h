@@ -151,6 +151,11 @@ struct LnResid {
   const LnRow* stats = nullptr;
   const float* g = nullptr;
   const float* b = nullptr;
+  // A product whose rows lie in two arrays: rows m1 .. M - 1 of A (and of R) are
+  // rows 0 .. of a2 (r2), same leading dimensions; a2 null: one array.
+  const void* a2 = nullptr;
+  const void* r2 = nullptr;
+  int m1 = 0;
 };
 
 // C[M][N] (ldc) = epi(A[M][K] (lda) * Bt[N][K]^T + bias[N] (+ residual)).

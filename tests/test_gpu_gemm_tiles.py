@@ -10,7 +10,7 @@ import pytest
 
 from paper_2607_28940_amd import inputs as I
 from paper_2607_28940_amd.inputs import ModelConfig
-from tests.parity_util import BF16_TOL, DeviceCase, check_err, log, oracle_request, score_err
+from tests.parity_util import BF16_TOL, FP32_TOL, DeviceCase, check_err, log, oracle_request, score_err
 
 pytestmark = pytest.mark.gpu
 
@@ -39,3 +39,54 @@ def test_score_independent_of_tile(oracle_mod, name):
     err = score_err(base[:n], oracle_request(oracle_mod.Oracle(model, w), wl, 0, cand=Xc[:n])[0])
     log(f"gemm tiles {name}: max err {err['max']:.3e} p99 {err['p99']:.3e}")
     check_err(err, BF16_TOL)
+
+
+F32 = {"d64": ModelConfig(64, 2, 256, 1, 2, rel_pos_buckets=16, dtype="f32"),
+       "d96": ModelConfig(96, 3, 112, 1, 2, rel_pos_buckets=16, dtype="f32")}
+
+
+@pytest.mark.parametrize("name", F32)
+def test_f32_score_independent_of_tile(oracle_mod, name):
+    """The fp32 projections: 16x16 outputs per wave and, from 1024 tiles of
+    32x32 on, 32x32; column counts that leave waves of a block idle, k of 4, 6
+    and 7 chunks. Bitwise independent of the number of rows, and the fp32 bar
+    against the oracle (which also covers 8 keys per softmax step on a history
+    of 70)."""
+    import torch
+    torch.cuda.set_device(0)
+    model = F32[name]
+    wl = I.custom_workload(model, cfg_id=84, L=[70], S=[3], C=[17000])
+    w = I.make_weights(model, ("sharp", "affine"))
+    run = DeviceCase(wl, w)
+    run.build([0])
+    Xc = I.request_tokens(wl, 0, I.STREAM_CANDIDATES)
+    base = run.score([0], cand=[Xc])[0]
+    for C in (1, 12, 13, 14, 29, 30, 61, 300, 4100):
+        assert np.array_equal(run.score([0], cand=[Xc[:C]])[0], base[:C]), C
+    n = 300
+    err = score_err(base[:n], oracle_request(oracle_mod.Oracle(model, w), wl, 0, cand=Xc[:n])[0])
+    log(f"f32 gemm tiles {name}: max err {err['max']:.3e}")
+    check_err(err, FP32_TOL)
+
+
+@pytest.mark.parametrize("S,C", [(0, 5), (1, 1), (33, 70), (129, 2200)])
+@pytest.mark.parametrize("name,model", [("bf16", MODELS["k4-k6"]), ("f32", F32["d64"])])
+def test_tokens_in_place_or_copied(name, model, S, C):
+    """The first layer reads aligned token arrays where they are (rows of two
+    arrays in one product, the serving rows ending inside a tile); tokens one
+    element off a 16-byte boundary are copied first. Same scores, bitwise."""
+    import torch
+    torch.cuda.set_device(0)
+    wl = I.custom_workload(model, cfg_id=85, L=[70], S=[S], C=[C])
+    run = DeviceCase(wl, I.make_weights(model, ("sharp", "affine")))
+    run.build([0])
+    xs = run.dev(np.concatenate([I.request_tokens(wl, 0, I.STREAM_SERVING), np.zeros((1, model.d_model), np.float32)]))
+    xc = run.dev(I.request_tokens(wl, 0, I.STREAM_CANDIDATES))
+
+    def off(x):
+        y = torch.empty(x.numel() + 1, dtype=x.dtype, device=x.device)[1:]
+        y.copy_(x.reshape(-1))
+        return y
+    a = run.cache.score([0], xs, [0, S], xc, [0, C]).cpu().numpy()
+    b = run.cache.score([0], off(xs), [0, S], off(xc), [0, C]).cpu().numpy()
+    assert np.all(np.isfinite(a)) and np.array_equal(a, b)
