@@ -912,27 +912,33 @@ __global__ __launch_bounds__(256, 2) void self_attn_mfma(const bf16* __restrict_
 
 // ============================================================================
 // Plain paged attention (fp32 models, head widths without an MFMA variant).
-// 64 queries per block, 4 lanes per query, each lane owning dh/4 features;
-// pages staged in LDS; eight keys per step of the online softmax, so that
-// their dot products overlap and the running state is updated once per step
-// (24 queries, 256 keys at d_h = 32: 67 us with one key at a time, 43 now).
+// 64 queries per block of 16 waves, 4 lanes per query, each lane owning dh/4
+// features. What bounds it at the sizes fp32 models serve (a few blocks) is
+// each query's serial chain of softmax steps, so a step takes eight keys (their
+// dot products overlap, the running state is updated once), four waves share
+// a group of 16 queries, each taking a quarter of every page's keys, their
+// states merged at the end, and the next page travels in registers while a
+// page in LDS is used. 16 queries, 256 keys at d_h = 32: 67 us with one key at
+// a time, 46 with eight, 18 with the four key quarters (the call 78 -> 50 us).
 // ============================================================================
+constexpr int kPlainSplits = 4;
+
 template <typename T, int DH>
-__global__ __launch_bounds__(256) void paged_attn_plain(const T* __restrict__ q, int ldq, T* __restrict__ out, int ldo,
-                                                        const T* __restrict__ pool, const int32_t* __restrict__ page_table,
-                                                        int max_pages, PageGeom g, int layer_slot,
-                                                        const AttnReq* __restrict__ reqs,
-                                                        const AttnTile* __restrict__ tiles, bool causal,
-                                                        const float* __restrict__ rel, int R, float scale_log2) {
-  constexpr int DP = DH / 4, NK = 8;
-  static_assert(kPage % NK == 0, "a step stays within the page's rows in LDS");
+__global__ __launch_bounds__(256 * kPlainSplits) void paged_attn_plain(
+    const T* __restrict__ q, int ldq, T* __restrict__ out, int ldo, const T* __restrict__ pool,
+    const int32_t* __restrict__ page_table, int max_pages, PageGeom g, int layer_slot, const AttnReq* __restrict__ reqs,
+    const AttnTile* __restrict__ tiles, bool causal, const float* __restrict__ rel, int R, float scale_log2) {
+  constexpr int DP = DH / 4, NK = 8, KEYS = kPage / kPlainSplits;
+  static_assert(KEYS % NK == 0, "a step stays within the split's rows in LDS");
+  typedef T tx4 __attribute__((ext_vector_type(4)));
   // rows of whole 16-byte units, so that a lane reads 4 features (K) or 4 keys (V) at once
   __shared__ __attribute__((aligned(16))) float sK[kPage][DH + 4];
   __shared__ __attribute__((aligned(16))) float sV[DH][kPage + 4];
   const AttnTile tile = tiles[blockIdx.x];
   if (tile.q_count <= 0) return;
   const AttnReq rq = reqs[tile.req];
-  const int h = tile.head, tid = threadIdx.x, qi = tid >> 2, part = tid & 3;
+  const int h = tile.head, tid = threadIdx.x, wave = tid >> 6, split = wave & (kPlainSplits - 1);
+  const int qi = (wave / kPlainSplits) * 16 + ((tid & 63) >> 2), part = tid & 3;
   const bool active = qi < tile.q_count;
   const int i = tile.q_begin + min(qi, tile.q_count - 1);
   const int row = i < rq.qa_n ? rq.qa_row + i : rq.qb_row + (i - rq.qa_n);
@@ -950,20 +956,44 @@ __global__ __launch_bounds__(256) void paged_attn_plain(const T* __restrict__ q,
   if (causal) n_pages = min(n_pages, (rq.pos0 + tile.q_begin + tile.q_count - 1) / kPage + 1);
   const int32_t* ptab = page_table + (size_t)rq.slot * max_pages;
 
-  for (int p = 0; p < n_pages; ++p) {
+  // a page in pieces of 4 elements: K's rows, then V^T's (4 neighbouring stored
+  // columns are 4 neighbouring keys)
+  constexpr int KU = kPage * DH / 4, NU = 2 * KU / (256 * kPlainSplits);
+  tx4 nx[NU];
+  auto fetch = [&](int p) {
     const size_t base = (size_t)ptab[p] * g.page_elems;
     const T* kp = pool + base + g.k_off(layer_slot, h);
     const T* vp = pool + base + g.v_off(layer_slot, h);
+#pragma unroll
+    for (int k = 0; k < NU; ++k) {
+      const int u = tid + 256 * kPlainSplits * k;
+      nx[k] = *reinterpret_cast<const tx4*>(u < KU ? kp + 4 * u : vp + 4 * (u - KU));
+    }
+  };
+  if (n_pages > 0) fetch(0);
+  for (int p = 0; p < n_pages; ++p) {
     const int valid = min(kPage, kv_len - p * kPage);
-    for (int e = tid; e < kPage * DH; e += 256) {
-      sK[e / DH][e % DH] = e / DH < valid ? (float)kp[e] : 0.f;
-      const int vr = e / kPage, key = vt_col(e % kPage);
-      sV[vr][key] = key < valid ? (float)vp[e] : 0.f;
+#pragma unroll
+    for (int k = 0; k < NU; ++k) {
+      const int u = tid + 256 * kPlainSplits * k;
+      floatx4 x;
+      if (u < KU) {
+        const int key = u / (DH / 4);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) x[t] = key < valid ? (float)nx[k][t] : 0.f;
+        *reinterpret_cast<floatx4*>(&sK[key][(u % (DH / 4)) * 4]) = x;
+      } else {
+        const int key = vt_col(((u - KU) % (kPage / 4)) * 4);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) x[t] = key + t < valid ? (float)nx[k][t] : 0.f;
+        *reinterpret_cast<floatx4*>(&sV[(u - KU) / (kPage / 4)][key]) = x;
+      }
     }
     __syncthreads();
+    if (p + 1 < n_pages) fetch(p + 1);
     if (active) {
       const int jn = causal ? min(valid, qpos - p * kPage + 1) : valid;  // keys this query sees on the page
-      for (int j0 = 0; j0 < jn; j0 += NK) {
+      for (int j0 = split * KEYS; j0 < min(jn, (split + 1) * KEYS); j0 += NK) {
         float sc[NK], mx = -INFINITY;
 #pragma unroll
         for (int u = 0; u < NK; ++u) {
@@ -1003,7 +1033,34 @@ __global__ __launch_bounds__(256) void paged_attn_plain(const T* __restrict__ q,
     }
     __syncthreads();
   }
-  if (active) {
+  // the splits' states pass through the idle K tile (a query's row; running
+  // max and sum in the V^T tile) and are folded into split 0's, in order; a
+  // split that saw no key adds nothing
+  static_assert(kPage >= 64 && DH * (kPage + 4) >= 128, "a query's state fits the tiles");
+  float* sml = &sV[0][0];
+  for (int s = 1; s < kPlainSplits; ++s) {
+    if (active && split == s) {
+#pragma unroll
+      for (int e = 0; e < DP; ++e) sK[qi][part * DP + e] = acc[e];
+      if (part == 0) {
+        sml[2 * qi] = m_run;
+        sml[2 * qi + 1] = l_run;
+      }
+    }
+    __syncthreads();
+    if (active && split == 0) {
+      const float ms = sml[2 * qi], ls = sml[2 * qi + 1];
+      if (ls != 0.f) {
+        const float m_new = fmaxf(m_run, ms), a0 = exp2f(m_run - m_new), a1 = exp2f(ms - m_new);
+        m_run = m_new;
+        l_run = fmaf(ls, a1, l_run * a0);
+#pragma unroll
+        for (int e = 0; e < DP; ++e) acc[e] = fmaf(sK[qi][part * DP + e], a1, acc[e] * a0);
+      }
+    }
+    __syncthreads();
+  }
+  if (active && split == 0) {
     const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
 #pragma unroll
     for (int e = 0; e < DP; ++e) out[(size_t)row * ldo + h * DH + part * DP + e] = (T)(acc[e] * inv);
@@ -1053,7 +1110,7 @@ hipError_t launch_paged_attention(bool bf, const void* q, int ldq, void* out, in
     return hipGetLastError();
   }
 #define TX_PP(T, DH)                                                                                              \
-  paged_attn_plain<T, DH><<<n_tiles, 256, 0, s>>>((const T*)q, ldq, (T*)out, ldo, (const T*)pool, page_table,     \
+  paged_attn_plain<T, DH><<<n_tiles, 256 * kPlainSplits, 0, s>>>((const T*)q, ldq, (T*)out, ldo, (const T*)pool, page_table,     \
                                                   max_pages, g, layer_slot, reqs, tiles, causal, rel, R, sl2)
   if (bf) {
     if (g.dh == 32) TX_PP(bf16, 32); else if (g.dh == 64) TX_PP(bf16, 64); else if (g.dh == 128) TX_PP(bf16, 128);

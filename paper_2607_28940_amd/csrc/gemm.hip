@@ -763,11 +763,12 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float* __restrict__ A
   }
 #pragma unroll
   for (int j = 0; j < TN; ++j) bp[j] = Bt + (size_t)min(n0 + 16 * j + l16, N - 1) * K + 4 * g;
-  floatx4 acc[TM][TN];
+  // even and odd chunks sum apart: two chains of half the length
+  floatx4 acc[TM][TN], odd[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < TN; ++j) acc[i][j] = odd[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   constexpr int D = 4;  // chunks of 16 columns in flight
   floatx4 a[D][TM], b[D][TN];
   auto load = [&](int s, int k0) {
@@ -788,10 +789,16 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float* __restrict__ A
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][i][t], b[s][j][t], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < TN; ++j) {
+            floatx4& c = s & 1 ? odd[i][j] : acc[i][j];
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][i][t], b[s][j][t], c, 0, 0, 0);
+          }
       if (k0 + 16 * (s + D) < K) load(s, k0 + 16 * (s + D));
     }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] += odd[i][j];
   // accumulator element v of tile (i, j): row m0 + 16 i + 4 g + v, column n0 + 16 j + l16
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
