@@ -881,22 +881,47 @@ struct TileCost {
 enum { T32x32, T32x64, T64x64, T64x128, T128x128, kPersistent, kTiles };
 static const TileCost kTileCost[kTiles] = {{32, 32, 2.0, 0.092},  {32, 64, 2.0, 0.115},   {64, 64, 2.2, 0.15},
                                            {64, 128, 4.3, 0.21}, {128, 128, 7.0, 0.28}, {PT, PT, 10.0, 1.0}};
-static int pick_tile(int M, int N, int K, bool persistent, int n_cu) {
+static double tile_us(int c, int M, int N, int K, int n_cu) {
+  const TileCost& t = kTileCost[c];
+  const double tiles = (double)((M + t.bm - 1) / t.bm) * (N / t.bn);
+  const double rounds = (double)(((long long)tiles + n_cu - 1) / n_cu);
+  const double compute = rounds * (t.fix + t.step * (K / RK));
+  const double l2 = t.fix + tiles * (t.bm + t.bn) * 2.0 * K / 16e6;
+  return std::max(compute, l2);
+}
+static int pick_tile(int M, int N, int K, bool persistent, int n_cu, double* us = nullptr) {
   int best = T128x128;
   double best_us = 1e30;
   for (int c = 0; c < kTiles; ++c) {
     if (c == kPersistent && !persistent) continue;
-    const TileCost& t = kTileCost[c];
-    const double tiles = (double)((M + t.bm - 1) / t.bm) * (N / t.bn);
-    const double rounds = (double)(((long long)tiles + n_cu - 1) / n_cu);
-    const double compute = rounds * (t.fix + t.step * (K / RK));
-    const double l2 = t.fix + tiles * (t.bm + t.bn) * 2.0 * K / 16e6;
-    const double us = std::max(compute, l2);
-    if (us < best_us) best_us = us, best = c;
+    const double t = tile_us(c, M, N, K, n_cu);
+    if (t < best_us) best_us = t, best = c;
   }
+  if (us) *us = best_us;
   return best;
 }
-bool gemm_ln_ok(int N, int K, int lda, int ldc) { return N % 128 == 0 && K % RK == 0 && lda % 8 == 0 && ldc % 8 == 0; }
+// Rows that the persistent kernel takes of a product of M: all, or those of its
+// full rounds over the CUs when the rows left over run faster in a launch of
+// smaller tiles than in a round that leaves most CUs idle. 66.5 k rows, N 1024
+// (4.06 rounds): K 1024 171 us whole, 142 + 10 split, K 4096 525 us, 430 + 29;
+// 33 k rows, N 1024, K 4096 (2.1 rounds) 304 us, 219 + 29; 11 k rows, N 1024,
+// K 4096 (1.1 rounds) 192 us, 112 + 35. The estimate charges 2 us for the second
+// launch and a twentieth of a round, so that ties stay whole.
+static int persistent_rows(int M, int N, int K, int n_cu) {
+  const int tiles_n = N / PT;
+  const long long tiles = (long long)((M + PT - 1) / PT) * tiles_n, rounds = tiles / n_cu;
+  const long long m1 = rounds * n_cu / tiles_n * PT;
+  if (rounds < 1 || tiles % n_cu == 0 || m1 <= 0 || m1 >= M) return M;
+  double rest = 0.0;
+  pick_tile((int)(M - m1), N, K, false, n_cu, &rest);
+  const double round = kTileCost[kPersistent].fix + kTileCost[kPersistent].step * (K / RK);
+  return tile_us(kPersistent, (int)m1, N, K, n_cu) + rest + 2.0 + 0.05 * round < tile_us(kPersistent, M, N, K, n_cu)
+             ? (int)m1
+             : M;
+}
+bool gemm_ln_ok(int N, int K, int lda, int ldc) {
+  return N % 128 == 0 && K % RK == 0 && (long long)N * K < (1ll << 31) && lda % 8 == 0 && ldc % 8 == 0;
+}
 
 hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const float* bias, const void* R, int ldr,
                        void* C, int ldc, int M, int N, int K, Epilogue epi, hipStream_t s, LnResid ln) {
@@ -931,6 +956,13 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
     if (ln.a2) return halves();
     return plain<float>(A, lda, Bt, bias, R, ldr, C, ldc, M, N, K, epi, ln, s);
   }
+  auto row_range = [&](long long m0, int mc) {  // rows m0 .. m0 + mc - 1 of one array
+    LnResid lc = ln;
+    if (lc.stats) lc.stats += m0;
+    return launch_gemm(bf, (const bf16*)A + m0 * lda, lda, Bt, bias,
+                       R ? (const void*)((const bf16*)R + m0 * ldr) : nullptr, ldr, (bf16*)C + m0 * ldc, ldc, mc, N, K,
+                       epi, s, lc);
+  };
   // The MFMA kernels address A, R and C with 32-bit byte offsets: a product
   // whose operands span 2^31 elements or more runs as several row chunks.
   {
@@ -939,12 +971,7 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
     if (M > rows_max && ln.a2) return halves();
     if (M > rows_max) {
       for (long long m0 = 0; m0 < M; m0 += rows_max) {
-        const int mc = (int)std::min(rows_max, (long long)M - m0);
-        LnResid lc = ln;
-        if (lc.stats) lc.stats += m0;
-        const hipError_t e = launch_gemm(bf, (const bf16*)A + m0 * lda, lda, Bt, bias,
-                                         R ? (const void*)((const bf16*)R + m0 * ldr) : nullptr, ldr,
-                                         (bf16*)C + m0 * ldc, ldc, mc, N, K, epi, s, lc);
+        const hipError_t e = row_range(m0, (int)std::min(rows_max, (long long)M - m0));
         if (e != hipSuccess) return e;
       }
       return hipSuccess;
@@ -954,8 +981,10 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
                        (((uintptr_t)Bt & 15) == 0) && (((uintptr_t)C & 15) == 0) && (((uintptr_t)R & 15) == 0) &&
                        (((uintptr_t)bias & 15) == 0) && (((uintptr_t)ln.g & 15) == 0) &&
                        (((uintptr_t)ln.b & 15) == 0) && ((((uintptr_t)ln.a2 | (uintptr_t)ln.r2) & 15) == 0);
-  if (ln.a2 && (N % 128 != 0 || K % RK != 0 || !aligned)) return halves();
-  if (N % 128 != 0 || K % RK != 0 || !aligned)
+  // (the weight's byte offsets have to fit 32 bits too)
+  const bool mfma = N % 128 == 0 && K % RK == 0 && (long long)N * K < (1ll << 31) && aligned;
+  if (ln.a2 && !mfma) return halves();
+  if (!mfma)
     return plain<bf16>(A, lda, Bt, bias, R, ldr, C, ldc, M, N, K, epi, ln, s);
   const bf16* a = (const bf16*)A;
   const bf16* b = (const bf16*)Bt;
@@ -972,6 +1001,13 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
   const bool persistent = persistent_shape(M, N, K, std::max({(long long)lda, (long long)ldc, (long long)ldr}));
   const int tile = pick_tile(M, N, K, persistent, n_cu);
   if (ln.a2 && tile == kPersistent) return halves();
+  if (tile == kPersistent) {
+    const int m1 = persistent_rows(M, N, K, n_cu);
+    if (m1 < M) {
+      const hipError_t e = row_range(0, m1);
+      return e != hipSuccess ? e : row_range(m1, M - m1);
+    }
+  }
   const int bm = kTileCost[tile].bm, tiles_n = N / kTileCost[tile].bn;
   const int tiles_m1 = ((ln.a2 ? ln.m1 : M) + bm - 1) / bm, tiles_m = tiles_m1 + (ln.a2 ? (M - ln.m1 + bm - 1) / bm : 0);
   const int n_tiles = tiles_n * tiles_m, per_xcd = (n_tiles + 7) / 8;

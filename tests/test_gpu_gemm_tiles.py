@@ -69,6 +69,24 @@ def test_f32_score_independent_of_tile(oracle_mod, name):
     check_err(err, FP32_TOL)
 
 
+@pytest.mark.parametrize("C", [9000, 33500])
+def test_rows_past_the_full_rounds(C):
+    """More 256x256 tiles than CUs with a part of a round left over (8 x 36 and
+    2 x 131 tiles of the d 512 projections on 256 CUs): the rows past the full
+    rounds run in smaller tiles. Same scores, bitwise, as in calls of few rows."""
+    import torch
+    torch.cuda.set_device(0)
+    model = MODELS["k8-k32"]
+    wl = I.custom_workload(model, cfg_id=88, L=[70], S=[3], C=[C])
+    run = DeviceCase(wl, I.make_weights(model, ("sharp", "affine")))
+    run.build([0])
+    Xc = I.request_tokens(wl, 0, I.STREAM_CANDIDATES)
+    base = run.score([0], cand=[Xc])[0]
+    assert np.all(np.isfinite(base))
+    for a, b in ((0, 300), (8100, 8300), (C // 2, C // 2 + 1), (max(0, 32768 - 200) if C > 32768 else 8185, C)):
+        assert np.array_equal(run.score([0], cand=[Xc[a:b]])[0], base[a:b]), (a, b)
+
+
 @pytest.mark.parametrize("S,C", [(0, 5), (1, 1), (33, 70), (129, 2200)])
 @pytest.mark.parametrize("name,model", [("bf16", MODELS["k4-k6"]), ("f32", F32["d64"])])
 def test_tokens_in_place_or_copied(name, model, S, C):
