@@ -268,7 +268,10 @@ struct PageDma {
 // waves a SIMD overlap their chains. Page p + 1's K is requested at the top of
 // page p's body, page p + 1's V^T once page p's PV has left the buffer; before
 // the PV each wave waits for its own V^T loads only (the K loads issued after
-// them may stay in flight) and the block meets at a barrier.
+// them may stay in flight) and the block meets at a barrier. At d_h = 64 four
+// blocks share a CU with both buffers twice (32 KB), so V^T travels with K
+// a whole page ahead (VB = 2) and that wait and barrier go: 58 -> 53 us per
+// layer for 8 users of 3-4 k tokens (64 blocks).
 //
 // active(p) (uniform in the wave): whether the wave has work on page p of the
 // range; qk(p, kfrag, pf): its scores and probabilities (mfma_qk_softmax).
@@ -279,14 +282,16 @@ struct PageDma {
 // below 64 the columns of the last page's keys from last_valid on are zeroed
 // in LDS (a prefix of the cached tokens: the page holds later tokens there).
 // ============================================================================
-template <int DH, class Active, class QK>
+constexpr int v_buffers(int dh) { return dh == 64 ? 2 : 1; }
+template <int DH, class Pin, class Active, class QK>
 __device__ __forceinline__ void page_loop(bf16* sKV, const bf16* __restrict__ pool, const int32_t* __restrict__ ptab,
                                           int n_pages, const PageGeom& g, int layer_slot, int h, int wave, int lane,
-                                          MfmaAcc<DH>& acc, Active active, QK qk, int last_valid = kPage) {
+                                          MfmaAcc<DH>& acc, Pin pin, Active active, QK qk, int last_valid = kPage) {
   const int l32 = lane & 31, hi = lane >> 5;
-  // K page buffers 0, 1, then the V^T page buffer
+  constexpr int VB = v_buffers(DH);
+  // K page buffers 0, 1, then the V^T page buffers
   bf16* const sK0 = sKV;
-  bf16* const sV = sKV + 2 * 64 * DH;
+  bf16* const sV0 = sKV + 2 * 64 * DH;
   const PageDma<DH> pd(wave, lane);
   // page-table window: lane l holds the pool index of page wbase + l of the
   // range; a page's index is read from its lane into a scalar, so the page
@@ -295,7 +300,8 @@ __device__ __forceinline__ void page_loop(bf16* sKV, const bf16* __restrict__ po
   int pwin = ptab[min(lane, n_pages - 1)];
   auto page = [&](int p) { return pool + (size_t)__builtin_amdgcn_readlane(pwin, p - wbase) * g.page_elems; };
   pd.load(page(0) + g.k_off(layer_slot, h), pd.koff, sK0);
-  pd.load(page(0) + g.v_off(layer_slot, h), pd.voff, sV);
+  pd.load(page(0) + g.v_off(layer_slot, h), pd.voff, sV0);
+  pin();
   // LDS byte offsets of the lane's MFMA fragments under the swizzles of
   // PageDma: K row kb * 32 + l32, slot 2 kk + hi at
   // kb * 64 DH * 2 + (kxor ^ 32 kk); V^T row 32 db + l32, slot 2 ks + hi at
@@ -306,13 +312,17 @@ __device__ __forceinline__ void page_loop(bf16* sKV, const bf16* __restrict__ po
   __syncthreads();
   for (int p = 0; p < n_pages; ++p) {
     const int b = (p & 1) * (64 * DH);
-    if (p + 1 < n_pages) pd.load(page(p + 1) + g.k_off(layer_slot, h), pd.koff, sK0 + (64 * DH - b));
+    bf16* const sV = sV0 + (VB == 2 ? b : 0);
+    if (p + 1 < n_pages) {
+      pd.load(page(p + 1) + g.k_off(layer_slot, h), pd.koff, sK0 + (64 * DH - b));
+      if (VB == 2) pd.load(page(p + 1) + g.v_off(layer_slot, h), pd.voff, sV0 + (64 * DH - b));
+    }
     const bool work = active(p);
     bf16x8 pf[4];
     // the K buffer's offset joins the base before the XORs (it lies above
     // their bits); the opaque copies keep the per-read addresses from being
     // hoisted out of the loop into registers held across it
-    int kx = kxor + 2 * b, vx = vxor + 2 * 2 * 64 * DH;
+    int kx = kxor + 2 * b, vx = vxor + 2 * 2 * 64 * DH + (VB == 2 ? 2 * b : 0);
     asm volatile("" : "+v"(kx), "+v"(vx));
     if (work) {
       auto kfrag = [&](int kb, int kk) {
@@ -320,7 +330,7 @@ __device__ __forceinline__ void page_loop(bf16* sKV, const bf16* __restrict__ po
       };
       qk(p, kfrag, pf);
     }
-    if (p > 0) {
+    if (VB == 1 && p > 0) {
       // V^T of page p (requested after page p - 1's PV) in LDS for every wave;
       // the DH / 32 K loads of page p + 1 issued since may stay in flight
       if (p + 1 < n_pages) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(DH / 32) : "memory");
@@ -340,7 +350,7 @@ __device__ __forceinline__ void page_loop(bf16* sKV, const bf16* __restrict__ po
       };
       mfma_pv<DH, true>(vfrag, pf, acc);
     }
-    __syncthreads();  // K and V^T of page p no longer read; K of page p + 1 landed
+    __syncthreads();  // K and V^T of page p no longer read; K (VB == 2: and V^T) of page p + 1 landed
     // no load is in flight here: the window moves when the next body's K
     // load (page p + 2) would leave it
     if (p + 2 - wbase >= 64 && p + 2 < n_pages) {
@@ -350,7 +360,7 @@ __device__ __forceinline__ void page_loop(bf16* sKV, const bf16* __restrict__ po
       // read of the window waits on the page loads issued after it)
       asm volatile("" : "+v"(pwin));
     }
-    if (p + 1 < n_pages) pd.load(page(p + 1) + g.v_off(layer_slot, h), pd.voff, sV);
+    if (VB == 1 && p + 1 < n_pages) pd.load(page(p + 1) + g.v_off(layer_slot, h), pd.voff, sV);
   }
 }
 
@@ -380,7 +390,7 @@ paged_attn_mfma(const bf16* __restrict__ q, int ldq, bf16* __restrict__ out, int
                 const int32_t* __restrict__ page_table, int max_pages, PageGeom g, int layer_slot,
                 const AttnReq* __restrict__ reqs, const AttnTile* __restrict__ tiles, const float* __restrict__ rel,
                 int R, float scale_log2, float bump_thr) {
-  __shared__ __attribute__((aligned(16))) bf16 sKV[3 * 64 * DH];
+  __shared__ __attribute__((aligned(16))) bf16 sKV[(2 + v_buffers(DH)) * 64 * DH];
   extern __shared__ float srel[];  // TABLE: R + 192 entries
 
   const AttnTile tile = tiles[blockIdx.x];
@@ -452,7 +462,16 @@ paged_attn_mfma(const bf16* __restrict__ q, int ldq, bf16* __restrict__ out, int
     };
     mfma_qk_softmax_fix<DH, true, true>(kfrag, qf, acc, scale_log2, fix, far ? far_bias : 0.f, pf, bump_thr);
   };
-  page_loop<DH>(sKV, pool, ptab, n_pages, g, layer_slot, h, wave, lane, acc, active, qk,
+  // The query fragments have landed before the loop: left to the compiler their
+  // loads sank below the barrier without a mask, and the wait for them inside
+  // the loop was one for the page in flight, on every page (d_h = 64, 8 users
+  // of 3-4 k tokens 73 -> 53 us per layer, 64 x 128 queries against 1024 keys
+  // 37.6 -> 33.7).
+  auto pin = [&]() {
+#pragma unroll
+    for (int kk = 0; kk < DH / 16; ++kk) asm volatile("" : "+v"(qf[kk]));
+  };
+  page_loop<DH>(sKV, pool, ptab, n_pages, g, layer_slot, h, wave, lane, acc, pin, active, qk,
                 !CAUSAL && kv_len % kPage ? kv_len % kPage : kPage);
   // the page buffers are free: waves 0-1 park their output rows in K buffer 0,
   // waves 2-3 in K buffer 1
@@ -477,7 +496,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const int32_t* __restrict__ page_table, int max_pages, PageGeom g, int layer_slot,
     const XTile* __restrict__ whole, const int32_t* __restrict__ whole_off, const XTile* __restrict__ split,
     const int32_t* __restrict__ split_off, float* __restrict__ partial, float scale_log2, float bump_thr) {
-  __shared__ __attribute__((aligned(16))) bf16 sKV[3 * 64 * DH];
+  __shared__ __attribute__((aligned(16))) bf16 sKV[(2 + v_buffers(DH)) * 64 * DH];
 
   // block b runs on XCD b % 8 and takes entry b / 8 of that XCD's lists, the
   // kv-split tiles (the longer ones) first
@@ -510,7 +529,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
       return key0 + kl < kv_len ? x : -INFINITY;
     }, pf, bump_thr);
   };
-  page_loop<DH>(sKV, pool, ptab, tile.page_end - p0, g, layer_slot, h, wave, lane, acc,
+  page_loop<DH>(sKV, pool, ptab, tile.page_end - p0, g, layer_slot, h, wave, lane, acc, [] {},
                 [&](int) { return wave_active; }, qk);
   if (tile.part >= 0) {
     // kv-split tile: fp32 O (unnormalised, features 32 db + 8 gq + 4 hi ..),
@@ -604,7 +623,13 @@ hipError_t launch_cross_attention(const void* q, int ldq, void* out, int ldo, co
 // into registers, the next page's while the current one is used (at d_h = 128
 // one wave per SIMD, 128 KB of pages in flight per CU against 64 KB for the
 // staged kernel), which is what a tile of the incremental append (16 new
-// tokens against thousands of cached ones) is bound by.
+// tokens against thousands of cached ones) is bound by. Pages fall into the
+// classes of the staged causal kernel (far: one constant in the exponentials'
+// offset; near: the bias from a padded LDS table; diagonal: also the mask): with a
+// clamp, compare and select per logit on every page a wave's page took 2.6 us
+// (8 users of 3-4 k tokens x 8 heads of 64: 160 -> 142 us per layer, 256 users
+// 355 -> 331, 3 users of 90-400 tokens 19.3 -> 14.4; at d_h = 128 and 256 users
+// of 7-8 k tokens the pages' bytes bound it, 1.32 ms at 6 TB/s either way).
 // ============================================================================
 template <int DH>
 struct PageFrags {
@@ -612,7 +637,7 @@ struct PageFrags {
   bf16x8 v[4][DH / 32];  // V^T rows 32 db + l32, stored columns 32 (ks / 2) + 16 (ks % 2) + 8 hi
 };
 
-template <int DH, bool CAUSAL>
+template <int DH>
 __global__ __launch_bounds__(256, 1) void paged_attn_decode(const bf16* __restrict__ q, int ldq, bf16* __restrict__ out,
                                                             int ldo, const bf16* __restrict__ pool,
                                                             const int32_t* __restrict__ page_table, int max_pages,
@@ -642,14 +667,19 @@ __global__ __launch_bounds__(256, 1) void paged_attn_decode(const bf16* __restri
 
   const int kv_len = rq.kv_len;
   int n_pages = (kv_len + kPage - 1) / kPage;
-  if (CAUSAL) n_pages = min(n_pages, (rq.pos0 + tile.q_begin + tile.q_count - 1) / kPage + 1);
+  n_pages = min(n_pages, (rq.pos0 + tile.q_begin + tile.q_count - 1) / kPage + 1);
   const int32_t* ptab = page_table + (size_t)rq.slot * max_pages;
-  // the head's relative-position table, per wave in LDS: the mask reads it
-  // without a vector-memory wait, which would also wait for the page in flight
-  __shared__ float s_rel[4][kDecodeMaxRel];
+  // the head's relative-position table, per wave in LDS (read without a
+  // vector-memory wait, which would also wait for the page in flight), padded as
+  // the staged kernel's: wrel[j] is the bias of distance kRelC - j in raw units
+  __shared__ float s_rel[4][kDecodeMaxRel + 192];
   float* wrel = s_rel[threadIdx.x >> 6];
-  if (CAUSAL)
-    for (int j = lane; j < R; j += 64) wrel[j] = rel[h * R + j];
+  const int kRelC = R + 96, last = max(R - 1, 0);
+  float far_bias = 0.f;
+  if (R > 0) {
+    for (int j = lane; j < R + 192; j += 64) wrel[j] = rel[h * R + min(max(kRelC - j, 0), last)] * bias_scale;
+    far_bias = rel[h * R + last] * bias_scale;
+  }
 
   auto fetch = [&](int p, PageFrags<DH>& f) {
     const bf16* base = pool + (size_t)ptab[p] * g.page_elems;
@@ -666,27 +696,36 @@ __global__ __launch_bounds__(256, 1) void paged_attn_decode(const bf16* __restri
       for (int db = 0; db < DH / 32; ++db)
         f.v[ks][db] = *reinterpret_cast<const bf16x8*>(vp + (size_t)db * 32 * kPage + 32 * (ks >> 1) + 16 * (ks & 1));
   };
-  // Causal pages whose every key lies at least R - 1 positions before the
-  // tile's first query are visible to all its queries with the bias at the
-  // last bucket: one added constant instead of the per-logit mask.
+  // Far pages: every key at least R - 1 positions before the tile's first
+  // query. Keys past the request's length lie past every query, on a page of
+  // the diagonal.
   const int q_first = rq.pos0 + tile.q_begin;
-  const float far_bias = (CAUSAL && R > 0) ? wrel[R - 1] * bias_scale : 0.f;
-  auto attend = [&](int p, PageFrags<DH>& f, bool tail) {
+  const float bump_thr = 8.f / scale_log2;
+  auto attend = [&](int p, PageFrags<DH>& f) {
     const int key0 = p * kPage;
-    const bool far = CAUSAL && !tail && key0 + kPage - 1 + max(R - 1, 0) <= q_first;
-    auto mask = [&](int kl, float x) {
-      if (far) return x + far_bias;
-      const int key = key0 + kl;
-      bool ok = key < kv_len;
-      if (CAUSAL) {
-        ok = ok && key <= qpos;
-        if (R > 0) x += wrel[min(max(qpos - key, 0), R - 1)] * bias_scale;
+    const bool far = key0 + kPage - 1 + last <= q_first;
+    auto fix = [&](floatx16(&s)[2]) {
+      if (far) return;
+      if (R > 0) {
+        // near pages hold distances up to R + 92 and, past the diagonal, down to -94
+        const float* u = wrel + (kRelC - (qpos - key0 - 4 * hi));
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) s[kb][v] += u[kb * 32 + 8 * (v >> 2) + (v & 3)];
       }
-      return ok ? x : -INFINITY;
+      if (key0 + kPage - 1 > q_first) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            s[kb][v] = key0 + kb * 32 + 8 * (v >> 2) + 4 * hi + (v & 3) <= qpos ? s[kb][v] : -INFINITY;
+      }
     };
-    mfma_attend_frags<DH, false>([&](int kb, int kk) { return f.k[kb][kk]; },
-                                 [&](int ks, int db) { return f.v[ks][db]; }, qf, acc, scale_log2, hi,
-                                 tail || (CAUSAL && (!far || R > 0)), mask);
+    bf16x8 pf[4];
+    mfma_qk_softmax_fix<DH, false, true>([&](int kb, int kk) { return f.k[kb][kk]; }, qf, acc, scale_log2, fix,
+                                         far ? far_bias : 0.f, pf, bump_thr);
+    mfma_pv<DH, false>([&](int ks, int db) { return f.v[ks][db]; }, pf, acc);
   };
   // keys past the request's length on the last page: V^T columns zeroed (the
   // page may hold anything there; their logits are masked)
@@ -708,20 +747,20 @@ __global__ __launch_bounds__(256, 1) void paged_attn_decode(const bf16* __restri
   int p = 0;
   for (; p + 1 < n_full; p += 2) {
     fetch(p + 1, fb);
-    attend(p, fa, false);
+    attend(p, fa);
     if (p + 2 < n_pages) fetch(p + 2, fa);
-    attend(p + 1, fb, false);
+    attend(p + 1, fb);
   }
   if (p < n_full) {
     if (p + 1 < n_pages) fetch(p + 1, fb);
-    attend(p, fa, false);
+    attend(p, fa);
     if (++p < n_pages) {
       zero_tail(p, fb);
-      attend(p, fb, true);
+      attend(p, fb);
     }
   } else if (p < n_pages) {
     zero_tail(p, fa);
-    attend(p, fa, true);
+    attend(p, fa);
   }
   if (l32 < tile.q_count) {
     const float inv = acc.l > 0.f ? 1.f / acc.l : 0.f;
@@ -1080,10 +1119,10 @@ hipError_t launch_paged_attention(bool bf, const void* q, int ldq, void* out, in
     bf16* oo = (bf16*)out;
     const bf16* pp = (const bf16*)pool;
     const unsigned blocks = (unsigned)((n_tiles + 3) / 4);
-#define TX_PD(DH, CZ)                                                                                              \
-  paged_attn_decode<DH, CZ><<<blocks, 256, 0, s>>>(qq, ldq, oo, ldo, pp, page_table, max_pages, g, layer_slot, reqs, \
+#define TX_PD(DH)                                                                                              \
+  paged_attn_decode<DH><<<blocks, 256, 0, s>>>(qq, ldq, oo, ldo, pp, page_table, max_pages, g, layer_slot, reqs, \
                                                     tiles, n_tiles, rel, R, sl2)
-    if (g.dh == 64) TX_PD(64, true); else TX_PD(128, true);
+    if (g.dh == 64) TX_PD(64); else TX_PD(128);
 #undef TX_PD
     return hipGetLastError();
   }
