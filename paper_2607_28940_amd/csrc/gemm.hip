@@ -852,7 +852,7 @@ static hipError_t plain(const void* A, int lda, const void* Bt, const float* bia
     case EPI_BIAS_GELU: TX_PL(EPI_BIAS_GELU); break;
     case EPI_BIAS_RESID: TX_PL(EPI_BIAS_RESID); break;
     case EPI_BIAS_RESLN: TX_PL(EPI_BIAS_RESLN); break;
-    default: return hipErrorInvalidValue;  // the LayerNorm-folding epilogues run on the persistent kernel only
+    default: return hipErrorInvalidValue;  // the LayerNorm-folding epilogues run on the MFMA kernels only
   }
 #undef TX_PL
   return hipGetLastError();
