@@ -17,6 +17,8 @@
 #include "tx_internal.h"
 #include "wave_reduce.h"
 
+#include <type_traits>
+
 namespace tx {
 
 constexpr float kLog2e = 1.4426950408889634f;
@@ -959,11 +961,15 @@ __global__ __launch_bounds__(256, 2) void self_attn_mfma(const bf16* __restrict_
 // states merged at the end, and the next page travels in registers while a
 // page in LDS is used. 16 queries, 256 keys at d_h = 32: 67 us with one key at
 // a time, 46 with eight, 18 with the four key quarters (the call 78 -> 50 us).
+// WAVES: waves a SIMD's registers are divided among, 4 for one block per CU, 8
+// (64 registers) for two. Two pay once there are more blocks than CUs (d_h 32
+// bf16, 256 users of 1000 tokens: 3.22 ms with one, 2.35 with two; at 4 blocks
+// one block's 72 registers keep more loads in flight, 26.6 against 27.7 us).
 // ============================================================================
 constexpr int kPlainSplits = 4;
 
-template <typename T, int DH>
-__global__ __launch_bounds__(256 * kPlainSplits) void paged_attn_plain(
+template <typename T, int DH, int WAVES>
+__global__ __launch_bounds__(256 * kPlainSplits, WAVES) void paged_attn_plain(
     const T* __restrict__ q, int ldq, T* __restrict__ out, int ldo, const T* __restrict__ pool,
     const int32_t* __restrict__ page_table, int max_pages, PageGeom g, int layer_slot, const AttnReq* __restrict__ reqs,
     const AttnTile* __restrict__ tiles, bool causal, const float* __restrict__ rel, int R, float scale_log2) {
@@ -1048,26 +1054,33 @@ __global__ __launch_bounds__(256 * kPlainSplits) void paged_attn_plain(
           sc[u] = j0 + u < jn ? x : -INFINITY;
           mx = fmaxf(mx, sc[u]);
         }
-        const float m_new = fmaxf(m_run, mx);  // finite: key j0 is visible
-        const float alpha = exp2f(m_run - m_new);
+        // -inf while a bias has masked every key so far: nothing is added then
+        const float m_new = fmaxf(m_run, mx), ref = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = exp2f(m_run - ref);
         m_run = m_new;
         l_run *= alpha;
 #pragma unroll
         for (int u = 0; u < NK; ++u) {
-          sc[u] = exp2f(sc[u] - m_new);
+          sc[u] = exp2f(sc[u] - ref);
           l_run += sc[u];
         }
+        // a key past the query's last adds nothing, whatever its value: zero times
+        // a value that is not finite would spoil the rows before its own
+        auto add_values = [&](auto all) {
 #pragma unroll
-        for (int e = 0; e < DP; ++e) {
-          float x = acc[e] * alpha;
+          for (int e = 0; e < DP; ++e) {
+            float x = acc[e] * alpha;
 #pragma unroll
-          for (int u = 0; u < NK; u += 4) {
-            const floatx4 v4 = *reinterpret_cast<const floatx4*>(&sV[part * DP + e][j0 + u]);
+            for (int u = 0; u < NK; u += 4) {
+              const floatx4 v4 = *reinterpret_cast<const floatx4*>(&sV[part * DP + e][j0 + u]);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) x = fmaf(sc[u + t], v4[t], x);
+              for (int t = 0; t < 4; ++t) x = fmaf(sc[u + t], all || j0 + u + t < jn ? v4[t] : 0.f, x);
+            }
+            acc[e] = x;
           }
-          acc[e] = x;
-        }
+        };
+        if (j0 + NK <= jn) add_values(std::true_type{});
+        else add_values(std::false_type{});
       }
     }
     __syncthreads();
@@ -1148,15 +1161,18 @@ hipError_t launch_paged_attention(bool bf, const void* q, int ldq, void* out, in
 #undef TX_PA
     return hipGetLastError();
   }
-#define TX_PP(T, DH)                                                                                              \
-  paged_attn_plain<T, DH><<<n_tiles, 256 * kPlainSplits, 0, s>>>((const T*)q, ldq, (T*)out, ldo, (const T*)pool, page_table,     \
-                                                  max_pages, g, layer_slot, reqs, tiles, causal, rel, R, sl2)
+#define TX_PP(T, DH, W)                                                                                                 \
+  paged_attn_plain<T, DH, W><<<n_tiles, 256 * kPlainSplits, 0, s>>>((const T*)q, ldq, (T*)out, ldo, (const T*)pool,     \
+                                                                    page_table, max_pages, g, layer_slot, reqs, tiles,   \
+                                                                    causal, rel, R, sl2)
+  const bool two = n_tiles > 256;  // more blocks than CUs
   if (bf) {
-    if (g.dh == 32) TX_PP(bf16, 32); else if (g.dh == 64) TX_PP(bf16, 64); else if (g.dh == 128) TX_PP(bf16, 128);
-    else return hipErrorInvalidValue;
+    if (g.dh == 32 && two) TX_PP(bf16, 32, 8);
+    else if (g.dh == 32) TX_PP(bf16, 32, 4); else if (g.dh == 64) TX_PP(bf16, 64, 4);
+    else if (g.dh == 128) TX_PP(bf16, 128, 4); else return hipErrorInvalidValue;
   } else {
-    if (g.dh == 32) TX_PP(float, 32); else if (g.dh == 64) TX_PP(float, 64); else if (g.dh == 128) TX_PP(float, 128);
-    else return hipErrorInvalidValue;
+    if (g.dh == 32) TX_PP(float, 32, 4); else if (g.dh == 64) TX_PP(float, 64, 4);
+    else if (g.dh == 128) TX_PP(float, 128, 4); else return hipErrorInvalidValue;
   }
 #undef TX_PP
   return hipGetLastError();

@@ -42,3 +42,24 @@ def test_plain_attention_edges(oracle_mod, dh, dtype):
     err = score_err(np.concatenate(scores), np.concatenate(refs))
     log(f"plain attention d_h {dh} {dtype}: keys {worst:.3e} scores max {err['max']:.3e}")
     check_err(err, FP32_TOL if dtype == "f32" else BF16_TOL)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_plain_attention_independent_of_grid(dtype):
+    """32-wide heads: more blocks than CUs take another variant of the kernel
+    (two blocks per CU). A user's cached keys and scores are bitwise the same
+    alone and among 130 users (4 heads: 520 blocks and more)."""
+    import torch
+    torch.cuda.set_device(0)
+    model = ModelConfig(128, 4, 256, 2, 2, rel_pos_buckets=40, dtype=dtype)
+    n, L = 130, [40 + (37 * r) % 200 for r in range(130)]
+    wl = I.custom_workload(model, cfg_id=90, L=L, S=[r % 4 for r in range(n)], C=[1 + (7 * r) % 90 for r in range(n)])
+    w = I.make_weights(model, ("sharp", "affine"))
+    many, one = DeviceCase(wl, w), DeviceCase(wl, w)
+    many.build(range(n))
+    scores = many.score(range(n))
+    for r in (0, 41, 129):
+        one.build([r])
+        assert np.array_equal(one.score([r])[0], scores[r]), r
+        for part in (0, 1):
+            assert torch.equal(one.cache.export(r, part, 1), many.cache.export(r, part, 1)), (r, part)
