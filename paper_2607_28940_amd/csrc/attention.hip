@@ -962,9 +962,14 @@ __global__ __launch_bounds__(256, 2) void self_attn_mfma(const bf16* __restrict_
 // page in LDS is used. 16 queries, 256 keys at d_h = 32: 67 us with one key at
 // a time, 46 with eight, 18 with the four key quarters (the call 78 -> 50 us).
 // WAVES: waves a SIMD's registers are divided among, 4 for one block per CU, 8
-// (64 registers) for two. Two pay once there are more blocks than CUs (d_h 32
-// bf16, 256 users of 1000 tokens: 3.22 ms with one, 2.35 with two; at 4 blocks
-// one block's 72 registers keep more loads in flight, 26.6 against 27.7 us).
+// (64 registers) for two, which d_h 32 takes once there are more blocks than
+// CUs: 256 users of 1000 tokens, causal 3.22 ms with one block, 2.31 with two
+// in bf16, 3.23 and 2.40 in fp32; at 4 blocks one block's registers keep more
+// loads in flight (26 against 28 us). Against the form before the quarters (four
+// waves, one key at a time, several blocks per CU) the same full grid, causal and
+// cross (16 + 200 queries a user): d_h 32 bf16 3.02 + 1.13 -> 2.31 + 0.83 ms,
+// fp32 3.06 + 1.18 -> 2.40 + 0.86, d_h 64 8.5 + 3.8 -> 6.1 + 2.5, d_h 128 32.5 +
+// 14.9 -> 13.1 + 5.6; so no grid needs that form any more.
 // ============================================================================
 constexpr int kPlainSplits = 4;
 
@@ -1171,7 +1176,8 @@ hipError_t launch_paged_attention(bool bf, const void* q, int ldq, void* out, in
     else if (g.dh == 32) TX_PP(bf16, 32, 4); else if (g.dh == 64) TX_PP(bf16, 64, 4);
     else if (g.dh == 128) TX_PP(bf16, 128, 4); else return hipErrorInvalidValue;
   } else {
-    if (g.dh == 32) TX_PP(float, 32, 4); else if (g.dh == 64) TX_PP(float, 64, 4);
+    if (g.dh == 32 && two) TX_PP(float, 32, 8);
+    else if (g.dh == 32) TX_PP(float, 32, 4); else if (g.dh == 64) TX_PP(float, 64, 4);
     else if (g.dh == 128) TX_PP(float, 128, 4); else return hipErrorInvalidValue;
   }
 #undef TX_PP
