@@ -128,6 +128,12 @@ __device__ __forceinline__ void mfma_qk_softmax_fix(KFrag kfrag, const bf16x8 (&
     for (int t = 0; t < 8; ++t) pf[ks][t] = (bf16)s[ks >> 1][8 * (ks & 1) + t];
 }
 
+// Whether a bias (raw units) may belong to a whole page's shift: it has to be
+// moderate. With one that masks (minus infinity, or overflowing to it) no maximum
+// would be taken off the page's exponentials, which overflow for logits past 88
+// and spoil the row; such pages take the bias per logit.
+__device__ __forceinline__ bool shift_ok(float bias) { return fabsf(bias) < 0x1p20f; }
+
 // The same with a mask per logit (`masked` uniform across the wave).
 template <int DH, bool FROM_LDS, class KFrag, class Mask>
 __device__ __forceinline__ void mfma_qk_softmax(KFrag kfrag, const bf16x8 (&qf)[DH / 16], MfmaAcc<DH>& acc,
@@ -427,6 +433,7 @@ paged_attn_mfma(const bf16* __restrict__ q, int ldq, bf16* __restrict__ out, int
       for (int j = tid; j < R + 192; j += 256) srel[j] = rel[h * R + min(max(kRelC - j, 0), last)] * bias_scale;
     far_bias = rel[h * R + last] * bias_scale;
   }
+  const bool fold = shift_ok(far_bias);
   const int wq0 = rq.pos0 + tile.q_begin + wave * 32;  // the wave's first and last query positions
   const int wq1 = rq.pos0 + tile.q_begin + min(wave * 32 + 31, tile.q_count - 1);
   const int qpos = rq.pos0 + i;
@@ -439,12 +446,13 @@ paged_attn_mfma(const bf16* __restrict__ q, int ldq, bf16* __restrict__ out, int
       }, pf, bump_thr);
       return;
     }
-    const bool far = key0 + kPage - 1 + last <= wq0;
+    const bool far = fold && key0 + kPage - 1 + last <= wq0;
     auto fix = [&](floatx16(&s)[2]) {
       if (far) return;
       if (R > 0) {
-        // near pages hold distances up to R + 92 and, past the diagonal, down to -94
-        const int d0 = qpos - key0 - 4 * hi;
+        // near pages hold distances up to R + 92 and, past the diagonal, down to
+        // -94; a farther page (when its bias cannot be folded) reads as the last
+        const int d0 = min(qpos - key0 - 4 * hi, R + 92);
         const float* u = srel + (kRelC - d0);
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
@@ -682,6 +690,7 @@ __global__ __launch_bounds__(256, 1) void paged_attn_decode(const bf16* __restri
     for (int j = lane; j < R + 192; j += 64) wrel[j] = rel[h * R + min(max(kRelC - j, 0), last)] * bias_scale;
     far_bias = rel[h * R + last] * bias_scale;
   }
+  const bool fold = shift_ok(far_bias);
 
   auto fetch = [&](int p, PageFrags<DH>& f) {
     const bf16* base = pool + (size_t)ptab[p] * g.page_elems;
@@ -705,12 +714,13 @@ __global__ __launch_bounds__(256, 1) void paged_attn_decode(const bf16* __restri
   const float bump_thr = 8.f / scale_log2;
   auto attend = [&](int p, PageFrags<DH>& f) {
     const int key0 = p * kPage;
-    const bool far = key0 + kPage - 1 + last <= q_first;
+    const bool far = fold && key0 + kPage - 1 + last <= q_first;
     auto fix = [&](floatx16(&s)[2]) {
       if (far) return;
       if (R > 0) {
-        // near pages hold distances up to R + 92 and, past the diagonal, down to -94
-        const float* u = wrel + (kRelC - (qpos - key0 - 4 * hi));
+        // near pages hold distances up to R + 92 and, past the diagonal, down to
+        // -94; a farther page (when its bias cannot be folded) reads as the last
+        const float* u = wrel + (kRelC - min(qpos - key0 - 4 * hi, R + 92));
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll

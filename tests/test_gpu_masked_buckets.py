@@ -22,9 +22,9 @@ def _cuda():
     torch.cuda.set_device(0)
 
 
-def _case(model, w, fill_byte=0xFF, n_append=0):
-    n = len(LENGTHS)
-    wl = I.custom_workload(model, cfg_id=91, L=LENGTHS, S=[1] * n, C=[1] * n, n_append=n_append)
+def _case(model, w, fill_byte=0xFF, n_append=0, L=LENGTHS):
+    n = len(L)
+    wl = I.custom_workload(model, cfg_id=91, L=L, S=[1] * n, C=[1] * n, n_append=n_append)
     run = DeviceCase(wl, w, fill_byte=fill_byte)
     run.build(range(n))
     return run
@@ -50,6 +50,35 @@ def test_masked_distances(oracle_mod, dh, dtype, low):
         worst = max(worst, e)
         assert np.isfinite(e) and e < (FP32_TOL if dtype == "f32" else BF16_TOL), (LENGTHS[r], e)
     log(f"masked distances d_h {dh} {dtype} {low}: worst {worst:.3e}")
+
+
+@pytest.mark.parametrize("low", [-np.inf, -3e38])
+@pytest.mark.parametrize("heads", [2, 4])
+@pytest.mark.parametrize("R,new", [(33, 0), (33, 9), (1030, 0)])
+def test_masked_last_bucket(heads, R, new, low):
+    """The last bucket masks every key past a window of R - 1 (histories of several
+    pages have pages wholly outside it), with logits of several hundred, whose
+    exponentials overflow unless a maximum is taken off. A bias of -1e4 leaves
+    nothing of those keys either (e^-1e4 is 0 in fp32), so cached keys and
+    values are bitwise the same; histories built whole (staged kernel, tables in
+    LDS and in memory) and with 9 events appended (register kernel)."""
+    model = ModelConfig(256, heads, 256, 2, 1, rel_pos_buckets=R)
+    L = LENGTHS + [1400]
+    got = []
+    for b in (-1e4, low):
+        w = I.make_weights(model, ("sharp", "affine"))
+        for e in range(model.n_enc_layers):
+            for i in (0, 2):  # Wq, Wk
+                w[17 * e + i] = I._round_storage(8 * w[17 * e + i], model.dtype)
+            w[17 * e + REL] = w[17 * e + REL].copy()
+            w[17 * e + REL][:, -1] = b
+        run = _case(model, w, n_append=new, L=L)
+        if new:
+            run.append(range(len(L)), 0, new)
+        got.append([run.cache.export(r, part, layer).float().cpu().numpy() for r in range(len(L))
+                    for part, layer in ((0, 1), (1, 1), (2, 0), (3, 0))])
+    for a, b in zip(*got):
+        assert np.all(np.isfinite(a)) and np.array_equal(a, b)
 
 
 @pytest.mark.parametrize("bad", [np.nan, np.inf])
