@@ -250,7 +250,12 @@ int kv_cache_append(tx_kv_cache* cache, int32_t n_req, const int32_t* req_ids /*
  *                      logit of candidate c of request i (sigmoid = click probability);
  *                      with n_actions = k, [sum C][k]: row candidate_offsets[i] + c holds
  *                      that candidate's probabilities over the k actions (sum 1)
- * A request with C_i = 0 contributes nothing. Errors: TX_E_NOCACHE (a request
+ * A request with C_i = 0 contributes nothing. A candidate's scores are bitwise
+ * the same whatever other candidates and requests share the call, except that
+ * in bf16 models with d_head 128 and dense cross-attention a request of 32
+ * pages or more (past 1984 cached tokens) may have its keys divided among
+ * blocks by the work of the whole call, which moves its scores by the rounding
+ * of another order of summing. Errors: TX_E_NOCACHE (a request
  * has no cache: cold start, App. D), TX_E_INVALID, TX_E_NOMEM, TX_E_HIP. */
 int score_candidates(const tx_kv_cache* cache, int32_t n_req, const int32_t* req_ids /* host */,
                      const void* serving, const int64_t* serving_offsets /* host */, const void* candidates,

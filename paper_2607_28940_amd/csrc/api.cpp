@@ -1317,7 +1317,8 @@ int run_score_pass(const tx_kv_cache* c, const int32_t* ids, const int64_t* kvle
     // GEMMs (rows r0 ..) and before the next layer's QKV GEMM (all rows) write
     // only their row statistics, and those GEMMs multiply the stored pre-LN
     // sums by the gain-scaled weights (EPI_LN); T is then not written at all
-    // (a model-level choice: a score does not depend on the batch it is in)
+    // (a model-level choice, so that it does not make a score depend on the
+    // batch it is in)
     const bool fold = m->ln_fold && gemm_ln_ok(d, d, d, d) && gemm_ln_ok(F, d, d, F);
     const bool fold_qkv = m->ln_fold && gemm_ln_ok(3 * d, d, d, 3 * d);
     const bool fold_in = l > 0 && fold_qkv, fold_out = !last && fold_qkv;

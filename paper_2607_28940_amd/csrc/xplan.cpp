@@ -12,12 +12,13 @@ namespace tx {
 // Worklist of the pipelined cross-attention (a1 of the scoring pass). Units
 // are (request, head, 128-query block) against all the request's pages. When
 // the batch leaves the GPU's resident blocks short of work, long units are
-// split by pages (kv-split): a unit of P pages takes ceil(P / Q) parts of at
-// least kXMinSplitPages, Q = the resident blocks' equal share of all pages
-// (tiles run longest first, so the makespan needs no finer parts: half that
-// share split a ragged batch's longest units for no gain and a merge of 11 us
-// per layer); the parts' partial results are merged afterwards. Columns (request, head, part) group the query blocks that read
-// the same pages; columns go to XCDs longest first (each XCD's least loaded
+// split by pages (kv-split): a unit of P >= kXWholePages pages takes ceil(P / Q)
+// parts of at least kXMinSplitPages, Q = the resident blocks' equal share of all
+// pages (tiles run longest first, so the makespan needs no finer parts: half
+// that share split a ragged batch's longest units for no gain and a merge of
+// 11 us per layer); the parts' partial results are merged afterwards. Columns
+// (request, head, part) group the query blocks that read the same pages;
+// columns go to XCDs longest first (each XCD's least loaded
 // first), and each XCD's list keeps a column's tiles adjacent, so that the
 // resident blocks of one XCD read a page slab from its L2 close in time.
 // Whole-request and kv-split columns form two tile sets, balanced together
@@ -42,7 +43,7 @@ void xattn_plan(const std::vector<AttnReq>& reqs, int H, int resident_blocks, in
   }
   int64_t quantum = std::max<int64_t>(kXMinSplitPages, (work + resident_blocks - 1) / resident_blocks);
   auto parts_of = [&](int pages) -> int {
-    if (pages <= quantum) return 1;
+    if (pages < kXWholePages || pages <= quantum) return 1;
     return (int)std::max<int64_t>(1, std::min<int64_t>((pages + quantum - 1) / quantum, pages / kXMinSplitPages));
   };
   // page quantum: raised to the smallest one for which the partial slots

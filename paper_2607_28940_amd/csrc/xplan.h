@@ -26,12 +26,20 @@ struct XPlan {
   int n_parts = 0;  // partial slots used (kv-split tiles)
 };
 
+// Histories of fewer pages are never split: whether one is, and into how many
+// parts, depends on the work of the whole batch, and parts change the order of
+// the sums. A score of a request with at most kXWholePages - 1 pages (1984
+// tokens) is therefore bitwise the same whatever users and candidates share the
+// call and however the call is cut into passes; past that it may differ by the
+// rounding of another order of summing. (Splitting from 8 pages on ran a call
+// of 8 users of 500-4000 tokens in 358 us against 404.)
+constexpr int kXWholePages = 32;
+
 // Fewest pages a kv-split part covers. A part costs a partial slot written and
 // read back (66 KB each way), a page of its block about 1 us; with 4 pages
-// instead of 16 (and the whole-request tiles in the same launch) a layer of 8
-// users of 500-4000 tokens went from 36 + 31 + 11 us (whole, split, merge) to
-// 29 + 7, of one user of 16384 (64-page parts before, 37 now) from 97 + 19 to
-// 79 + 8.
+// instead of 16 (and the whole-request tiles in the same launch) a layer of one
+// user of 16384 (64-page parts before, 37 now) went from 97 + 19 us (split, merge)
+// to 79 + 8.
 constexpr int kXMinSplitPages = 4;
 
 // Tiles for the requests of one cross-attention launch (queries of request r:

@@ -76,6 +76,7 @@ static void check_plan(const std::vector<tx::AttnReq>& reqs, int H, int blocks, 
         EXPECT(t.part < p.n_parts);
         if (t.part < p.n_parts) ++part_use[t.part];
         EXPECT(t.page_end - t.page_begin >= tx::kXMinSplitPages);
+        EXPECT(pages >= 32);  // shorter histories run whole in every batch
       } else {
         EXPECT(t.page_begin == 0 && t.page_end == pages);
       }
@@ -109,7 +110,7 @@ static void check_plans() {
   // headline-like batch: no request is split
   for (int r = 0; r < 64; ++r) reqs.push_back({r * 576, 64, 64 * 576 + r * 512, 512, 4096, 0, r, 0});
   check_plan(reqs, 8, 512, 512, 0);
-  // four long requests with a ragged tail page: split, every part >= 16 pages
+  // four long requests with a ragged tail page: split
   reqs.clear();
   for (int r = 0; r < 4; ++r) reqs.push_back({r * 600, 64, 4 * 600 + r * 536, 536 + r, 16384 - 37 * r, 0, 10 + r, 0});
   check_plan(reqs, 8, 512, 512, 1);
@@ -133,6 +134,11 @@ static void check_plans() {
     row += S + C;
   }
   check_plan(reqs, 4, 64, 512, -1);
+  // alone on an idle GPU: whole up to 31 pages, split from 32 on
+  for (int pages : {7, 8, 9, 16, 24, 31, 32, 33, 64}) {
+    reqs.assign(1, tx::AttnReq{0, 4, 4, 20, pages * 64 - 5, 0, 1, 0});
+    check_plan(reqs, 8, 768, 512, pages >= 32);
+  }
 }
 
 int main() {

@@ -68,7 +68,7 @@ def test_kv_split_vs_oracle(O):
     """Few requests with long caches: the cross-attention work list splits the
     long request's pages over several tiles per (head, query block) and merges
     their partial results (log-sum-exp), since a whole-request tile would leave
-    the GPU idle (3000 cached tokens = 47 pages, in parts of at least 16). The
+    the GPU idle (3000 cached tokens = 47 pages, in parts of at least 4). The
     scores match the oracle; reordering the candidates does not change the
     plan, and every candidate's scores are bitwise unchanged."""
     model = SMALL_BF16[0][1]
