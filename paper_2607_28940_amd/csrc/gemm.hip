@@ -14,12 +14,14 @@
 // lane's accumulator holds 4 consecutive output columns of one row. Large
 // products run on a persistent kernel (one block per CU walking 256x256 tiles,
 // see gemm_bf16_p4); the others on one block per tile of 32x32 to 128x128
-// (gemm_bf16_ring). Tiles are numbered so that each
-// of the 8 XCDs (the hardware deals workgroup b to XCD b % 8) works through a
-// contiguous range of them, walked in groups of row blocks so that operand
+// (gemm_bf16_ring) or of 128x128 with two blocks per CU (gemm_bf16_pair), by
+// estimated time (gemm_plan.h). Tiles are numbered so that each of the 8 XCDs
+// (the hardware deals workgroup b to XCD b % 8) works through a contiguous
+// range of them, walked in groups of row blocks so that operand
 // blocks are reused from that XCD's L2.
 #include <atomic>
 
+#include "gemm_plan.h"
 #include "tx_internal.h"
 
 #include <algorithm>
@@ -140,7 +142,7 @@ __device__ __forceinline__ void ring_tail(F f) {
   if constexpr (I + 1 < S) ring_tail<S, I + 1>(f);
 }
 
-constexpr int RK = 64;  // k columns per stage
+constexpr int RK = kRingK;  // k columns per stage
 
 // Ring kernel: one block of four waves per BM x BN output tile, for products
 // with too few 256x256 tiles for the persistent kernel. What bounds a small
@@ -312,6 +314,109 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring(const bf16* __restrict__ A
   }
 }
 
+// Pair kernel: one block of four waves per 128x128 output tile, two blocks per
+// CU, operands staged global -> registers -> LDS (rows padded by 16 bytes, no
+// bank conflicts), double-buffered, requested one k step ahead. For products
+// with many 128x128 tiles that are none of the persistent kernel's (N not a
+// multiple of 256, short K): there the other block's MFMAs run through one
+// block's prologue, epilogue and barriers, which the ring kernel, alone on its
+// CU, does not have: 66500 rows of N 1152, K 384 143 us on the ring, 130 here;
+// N 384, K 128 38.7, 32.9. Sums in the order
+// of the other kernels.
+constexpr int GM = 128, GN = 128, GK = kRingK, GLD = GK + 8;
+
+template <int EPI>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_pair(const bf16* __restrict__ A, int lda,
+                                                         const bf16* __restrict__ Bt, const float* __restrict__ bias,
+                                                         const void* __restrict__ R, int ldr, void* __restrict__ C,
+                                                         int ldc, int M, int N, int K, int tiles_m1, int tiles_m,
+                                                         int tiles_n, LnResid ln) {
+  __shared__ __attribute__((aligned(16))) bf16 sA[2][GM * GLD];
+  __shared__ __attribute__((aligned(16))) bf16 sB[2][GN * GLD];
+
+  const int n_tiles = tiles_m * tiles_n, per_xcd = (n_tiles + 7) >> 3;
+  const int t = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+  if (t >= n_tiles) return;
+  const int mt = t / tiles_n, n0 = (t % tiles_n) * GN;
+  // row tiles from tiles_m1 on lie in the second array (see LnResid::a2)
+  const bool second = mt >= tiles_m1;
+  const int row0 = second ? ln.m1 : 0;                        // output row of the array's row 0
+  const int rows = second ? M - ln.m1 : (ln.a2 ? ln.m1 : M);  // rows of the array
+  const int m0 = (second ? mt - tiles_m1 : mt) * GM;
+  const bf16* const Ar = second ? (const bf16*)ln.a2 : A;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int l32 = lane & 31, hi = lane >> 5;
+
+  // 128 rows x 8 chunks of 16 B per operand, 4 chunks per thread (rows past the
+  // array's last repeat it; their results are not stored)
+  bf16x8 ra[4], rb[4];
+  auto gload = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int c = tid + 256 * u, r = c >> 3, col = (c & 7) * 8;
+      ra[u] = *reinterpret_cast<const bf16x8*>(Ar + (size_t)min(m0 + r, rows - 1) * lda + k0 + col);
+      rb[u] = *reinterpret_cast<const bf16x8*>(Bt + (size_t)(n0 + r) * K + k0 + col);
+    }
+  };
+  auto lstore = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int c = tid + 256 * u, r = c >> 3, col = (c & 7) * 8;
+      *reinterpret_cast<bf16x8*>(&sA[buf][r * GLD + col]) = ra[u];
+      *reinterpret_cast<bf16x8*>(&sB[buf][r * GLD + col]) = rb[u];
+    }
+  };
+
+  floatx16 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+  const int nk = K / GK;
+  gload(0);
+  lstore(0);
+  __syncthreads();
+  for (int kt = 0; kt < nk; ++kt) {
+    const int cur = kt & 1;
+    if (kt + 1 < nk) gload((kt + 1) * GK);
+#pragma unroll
+    for (int ks = 0; ks < GK / 16; ++ks) {
+      bf16x8 fw[2], fx[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        fw[i] = *reinterpret_cast<const bf16x8*>(&sB[cur][(wn * 64 + i * 32 + l32) * GLD + ks * 16 + hi * 8]);
+        fx[i] = *reinterpret_cast<const bf16x8*>(&sA[cur][(wm * 64 + i * 32 + l32) * GLD + ks * 16 + hi * 8]);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          if (epi_lnfold(EPI))  // fp16 operands (see gemm_bf16_p4)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fw[i]),
+                                                               __builtin_bit_cast(f16x8, fx[j]), acc[i][j], 0, 0, 0);
+          else
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[i], fx[j], acc[i][j], 0, 0, 0);
+        }
+    }
+    if (kt + 1 < nk) lstore(cur ^ 1);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int m = m0 + wm * 64 + j * 32 + l32;
+    if (m >= rows) continue;
+    const bf16* rrow = (const bf16*)(second ? ln.r2 : R) + (size_t)m * ldr;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      store_acc<EPI>(acc[i][j], row0 + m, n0 + wn * 64 + i * 32 + 4 * hi, bias, rrow, C, ldc, ln);
+  }
+}
+
 constexpr int kGroupM = 8;  // row blocks that share each column block in turn (L2 reuse)
 
 // Persistent four-wave kernel: one block per CU walks a run of 256x256 output
@@ -330,7 +435,7 @@ constexpr int kGroupM = 8;  // row blocks that share each column block in turn (
 // evenly over the step instead of arriving in one burst. The load stream runs
 // across tile boundaries and the epilogue parks results in an LDS area of its
 // own, so the pipeline never drains between tiles.
-constexpr int PT = 256, PK = 64, kPStage = 2 * PT * PK;
+constexpr int kPStage = 2 * PT * PK;
 
 #define TX_LGKM_BARRIER() asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
 
@@ -858,69 +963,8 @@ static hipError_t plain(const void* A, int lda, const void* Bt, const float* bia
   return hipGetLastError();
 }
 
-// Shapes the persistent kernel takes: N a multiple of the tile, K of two k
-// steps and at least four, M at least 2048 rows (below, its launch covers too
-// few of the CUs), element offsets within int32.
-static bool persistent_shape(int M, int N, int K, long long ld_max) {
-  return N % PT == 0 && K % (2 * PK) == 0 && K >= 4 * PK && M >= 2048 && (long long)M * ld_max < (1ll << 31) &&
-         (long long)N * K < (1ll << 31);
-}
-
-// Tile choice of the bf16 MFMA products: the least estimated time, from the
-// measured cost of each tile's round over the CUs (us: a fixed part, prologue
-// and epilogue, and a part per 64 columns of k) and the rate at which the L2s
-// deliver operands to all CUs (about 16 MB per us). Small tiles spread a small
-// M over more CUs, large ones read less per flop. On the MI355X the estimate
-// is within 20% of the measured time for M from 34 to 18000 at (N, K) of the
-// 512- and 1024-wide models' projections, and picks a tile within 15% of the
-// fastest. kPersistent is the 256x256 kernel.
-struct TileCost {
-  int bm, bn;
-  double fix, step;
-};
-enum { T32x32, T32x64, T64x64, T64x128, T128x128, kPersistent, kTiles };
-static const TileCost kTileCost[kTiles] = {{32, 32, 2.0, 0.092},  {32, 64, 2.0, 0.115},   {64, 64, 2.2, 0.15},
-                                           {64, 128, 4.3, 0.21}, {128, 128, 7.0, 0.28}, {PT, PT, 10.0, 1.0}};
-static double tile_us(int c, int M, int N, int K, int n_cu) {
-  const TileCost& t = kTileCost[c];
-  const double tiles = (double)((M + t.bm - 1) / t.bm) * (N / t.bn);
-  const double rounds = (double)(((long long)tiles + n_cu - 1) / n_cu);
-  const double compute = rounds * (t.fix + t.step * (K / RK));
-  const double l2 = t.fix + tiles * (t.bm + t.bn) * 2.0 * K / 16e6;
-  return std::max(compute, l2);
-}
-static int pick_tile(int M, int N, int K, bool persistent, int n_cu, double* us = nullptr) {
-  int best = T128x128;
-  double best_us = 1e30;
-  for (int c = 0; c < kTiles; ++c) {
-    if (c == kPersistent && !persistent) continue;
-    const double t = tile_us(c, M, N, K, n_cu);
-    if (t < best_us) best_us = t, best = c;
-  }
-  if (us) *us = best_us;
-  return best;
-}
-// Rows that the persistent kernel takes of a product of M: all, or those of its
-// full rounds over the CUs when the rows left over run faster in a launch of
-// smaller tiles than in a round that leaves most CUs idle. 66.5 k rows, N 1024
-// (4.06 rounds): K 1024 171 us whole, 142 + 10 split, K 4096 525 us, 430 + 29;
-// 33 k rows, N 1024, K 4096 (2.1 rounds) 304 us, 219 + 29; 11 k rows, N 1024,
-// K 4096 (1.1 rounds) 192 us, 112 + 35. The estimate charges 2 us for the second
-// launch and a twentieth of a round, so that ties stay whole.
-static int persistent_rows(int M, int N, int K, int n_cu) {
-  const int tiles_n = N / PT;
-  const long long tiles = (long long)((M + PT - 1) / PT) * tiles_n, rounds = tiles / n_cu;
-  const long long m1 = rounds * n_cu / tiles_n * PT;
-  if (rounds < 1 || tiles % n_cu == 0 || m1 <= 0 || m1 >= M) return M;
-  double rest = 0.0;
-  pick_tile((int)(M - m1), N, K, false, n_cu, &rest);
-  const double round = kTileCost[kPersistent].fix + kTileCost[kPersistent].step * (K / RK);
-  return tile_us(kPersistent, (int)m1, N, K, n_cu) + rest + 2.0 + 0.05 * round < tile_us(kPersistent, M, N, K, n_cu)
-             ? (int)m1
-             : M;
-}
 bool gemm_ln_ok(int N, int K, int lda, int ldc) {
-  return N % 128 == 0 && K % RK == 0 && (long long)N * K < (1ll << 31) && lda % 8 == 0 && ldc % 8 == 0;
+  return N % 128 == 0 && K % kRingK == 0 && (long long)N * K < (1ll << 31) && lda % 8 == 0 && ldc % 8 == 0;
 }
 
 hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const float* bias, const void* R, int ldr,
@@ -982,7 +1026,7 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
                        (((uintptr_t)bias & 15) == 0) && (((uintptr_t)ln.g & 15) == 0) &&
                        (((uintptr_t)ln.b & 15) == 0) && ((((uintptr_t)ln.a2 | (uintptr_t)ln.r2) & 15) == 0);
   // (the weight's byte offsets have to fit 32 bits too)
-  const bool mfma = N % 128 == 0 && K % RK == 0 && (long long)N * K < (1ll << 31) && aligned;
+  const bool mfma = N % 128 == 0 && K % kRingK == 0 && (long long)N * K < (1ll << 31) && aligned;
   if (ln.a2 && !mfma) return halves();
   if (!mfma)
     return plain<bf16>(A, lda, Bt, bias, R, ldr, C, ldc, M, N, K, epi, ln, s);
@@ -1019,6 +1063,9 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
 #define TX_GR(E, BM, BN, MI, NI, S)                                                                                  \
   gemm_bf16_ring<E, BM, BN, MI, NI, S><<<8 * per_xcd, 256, 0, s>>>(a, lda, b, bias, R, ldr, C, ldc, M, N, K, tiles_m1, \
                                                                    tiles_m, tiles_n, M <= N, ln)
+#define TX_GPAIR(E)                                                                                                   \
+  gemm_bf16_pair<E><<<8 * per_xcd, 256, 0, s>>>(a, lda, b, bias, R, ldr, C, ldc, M, N, K, tiles_m1, tiles_m, tiles_n, \
+                                                ln)
 #define TX_GT(E)                                          \
   switch (tile) {                                         \
     case T32x32: TX_GR(E, 32, 32, 1, 1, 16); break;       \
@@ -1026,6 +1073,7 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
     case T64x64: TX_GR(E, 64, 64, 1, 1, 4); break;        \
     case T64x128: TX_GR(E, 64, 128, 1, 2, 6); break;      \
     case T128x128: TX_GR(E, 128, 128, 2, 2, 4); break;    \
+    case kPair: TX_GPAIR(E); break;                       \
     default: TX_GP4(E); break;                            \
   }
   switch (epi) {
@@ -1037,6 +1085,7 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
     case EPI_LN_GELU: TX_GT(EPI_LN_GELU); break;
   }
 #undef TX_GT
+#undef TX_GPAIR
 #undef TX_GR
 #undef TX_GP4
   return hipGetLastError();

@@ -1,0 +1,75 @@
+"""Tile choice of the bf16 products (csrc/gemm_plan.h), compiled for the host:
+shapes whose kernel was measured, and bounds of the persistent kernel's share
+of the rows."""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+TILES = ["32x32", "32x64", "64x64", "64x128", "128x128", "pair", "persistent"]
+SRC = """
+#include "gemm_plan.h"
+extern "C" int plan_tile(int M, int N, int K, long long ld, int n_cu) {
+  return tx::pick_tile(M, N, K, tx::persistent_shape(M, N, K, ld), n_cu);
+}
+extern "C" int plan_rows(int M, int N, int K, int n_cu) { return tx::persistent_rows(M, N, K, n_cu); }
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(SRC)
+    out = str(d / "plan.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-Wno-unused-variable", "-shared", "-fPIC",
+                    "-I" + os.path.join(ROOT, "paper_2607_28940_amd", "csrc"), str(d / "plan.cpp"), "-o", out],
+                   check=True)
+    lib = ctypes.CDLL(out)
+    lib.plan_tile.argtypes = [ctypes.c_int] * 3 + [ctypes.c_longlong, ctypes.c_int]
+    lib.plan_rows.argtypes = [ctypes.c_int] * 4
+    return lib
+
+
+def tile(plan, M, N, K):
+    return TILES[plan.plan_tile(M, N, K, max(N, K), 256)]
+
+
+# (M, N, K): the kernel, and a slower one (us, each launch on operands of its own)
+MEASURED = [
+    ((66500, 1152, 384), "pair"),        # 130; 128x128 ring 143
+    ((33000, 384, 128), "pair"),         # 18.0; 21.3
+    ((131200, 384, 384), "pair"),        # 92.6; 102
+    ((66500, 640, 640), "pair"),         # 107; 112
+    ((50000, 1920, 640), "pair"),        # the pair kernel's own range
+    ((33000, 512, 2048), "persistent"),  # 91.3; 107.5
+    ((4000, 1536, 512), "persistent"),   # 16.4; 18.1
+    ((10240, 2048, 512), "persistent"),  # 30.3; 32.0
+    ((24000, 256, 1024), "persistent"),  # 27.5; 30.6
+    ((66500, 4096, 1024), "persistent"),
+    ((6327, 512, 2048), "128x128"),      # 18.9; pair 29.7, persistent 39.8
+    ((3000, 512, 2048), "64x128"),       # 12.7; 128x128 16.2
+    ((600, 1024, 1024), "64x64"),        # 6.1; 128x128 10.4, pair 16.0
+    ((34, 512, 2048), "32x32"),          # 6.3; 128x128 12.8, pair 25.2
+]
+
+
+@pytest.mark.parametrize("shape,want", MEASURED)
+def test_measured_choices(plan, shape, want):
+    assert tile(plan, *shape) == want
+
+
+def test_every_choice_is_possible(plan):
+    rng = random.Random(1)
+    seen = set()
+    for _ in range(20000):
+        M, N, K = int(2 ** rng.uniform(0, 18)), 128 * rng.randrange(1, 65), 64 * rng.randrange(1, 129)
+        t = tile(plan, M, N, K)
+        seen.add(t)
+        if t == "persistent":
+            assert N % 256 == 0 and K % 128 == 0 and K >= 256 and M >= 2048
+            m1 = plan.plan_rows(M, N, K, 256)
+            assert 0 < m1 <= M and (m1 == M or m1 % 256 == 0)
+    assert seen == set(TILES)

@@ -87,6 +87,35 @@ def test_rows_past_the_full_rounds(C):
         assert np.array_equal(run.score([0], cand=[Xc[a:b]])[0], base[a:b]), (a, b)
 
 
+@pytest.mark.parametrize("S,C", [(0, 20000), (33, 20000), (40, 20051)])
+def test_pair_kernel(oracle_mod, S, C):
+    """Many 128x128 tiles of products that are none of the persistent kernel's
+    (N 384 and 1152, K 128 and 384): two blocks per CU. The rows of one array
+    and of two, partial last tiles. Bitwise as in calls of few rows, and in
+    place as copied; the first scores against the oracle."""
+    import torch
+    torch.cuda.set_device(0)
+    model = ModelConfig(384, 3, 128, 1, 2, rel_pos_buckets=16)
+    wl = I.custom_workload(model, cfg_id=93, L=[70], S=[S], C=[C])
+    w = I.make_weights(model, ("sharp", "affine"))
+    run = DeviceCase(wl, w)
+    run.build([0])
+    Xc = I.request_tokens(wl, 0, I.STREAM_CANDIDATES)
+    base = run.score([0], cand=[Xc])[0]
+    assert np.all(np.isfinite(base))
+    for a, b in ((0, 300), (C // 2, C // 2 + 130), (C - 200, C)):
+        assert np.array_equal(run.score([0], cand=[Xc[a:b]])[0], base[a:b]), (a, b)
+    xc = run.dev(np.concatenate([Xc.reshape(-1), np.zeros(1, np.float32)]))
+    off = torch.empty_like(xc)[1:]
+    off.copy_(xc[:-1])
+    xs = run.dev(np.concatenate([I.request_tokens(wl, 0, I.STREAM_SERVING), np.zeros((1, 384), np.float32)]))
+    copied = run.cache.score([0], xs, [0, S], off, [0, C]).cpu().numpy().astype(np.float64)
+    assert np.array_equal(copied, base)
+    err = score_err(base[:200], oracle_request(oracle_mod.Oracle(model, w), wl, 0, cand=Xc[:200])[0])
+    log(f"pair kernel S {S} C {C}: max err {err['max']:.3e}")
+    check_err(err, BF16_TOL)
+
+
 @pytest.mark.parametrize("S,C", [(0, 5), (1, 1), (33, 70), (129, 2200)])
 @pytest.mark.parametrize("name,model", [("bf16", MODELS["k4-k6"]), ("f32", F32["d64"])])
 def test_tokens_in_place_or_copied(name, model, S, C):
