@@ -52,11 +52,13 @@ inline double tile_us(int c, int M, int N, int K, int n_cu) {
   return std::max(us, t.few_fix + tiles * (t.bm + t.bn) * 2.0 * K / (kL2MBPerUs * 1e6));
 }
 
+constexpr int kPersistentRows = 2048;  // below, its launch covers too few of the CUs
+
 // Products the persistent kernel takes: N a multiple of the tile, K of two k
-// steps and at least four, M at least 2048 rows (below, its launch covers too
-// few of the CUs), element offsets within int32 (ld_max: the longest row).
+// steps and at least four, enough rows, element offsets within int32 (ld_max:
+// the longest row).
 inline bool persistent_shape(int M, int N, int K, long long ld_max) {
-  return N % PT == 0 && K % (2 * PK) == 0 && K >= 4 * PK && M >= 2048 && (long long)M * ld_max < (1ll << 31) &&
+  return N % PT == 0 && K % (2 * PK) == 0 && K >= 4 * PK && M >= kPersistentRows && (long long)M * ld_max < (1ll << 31) &&
          (long long)N * K < (1ll << 31);
 }
 
@@ -81,12 +83,13 @@ inline int pick_tile(int M, int N, int K, bool persistent, int n_cu, double* us 
 // so that ties stay whole. 66500 rows, N 1024 (4.06 rounds): K 1024 151 us
 // whole, 133 split, K 4096 507 and 443; 33000 rows, N 512, K 2048 93 and 71.
 // Over 240 products of 1 to 9 rounds the choice is 0.1% off the better one on
-// average and at most 4% behind the whole launch.
+// average and at most 4% behind the whole launch. Rows split off are as many as
+// the kernel takes (a round of a wide output may have fewer: those stay whole).
 inline int persistent_rows(int M, int N, int K, int n_cu) {
   const int tiles_n = N / PT;
   const long long tiles = (long long)((M + PT - 1) / PT) * tiles_n, rounds = tiles / n_cu;
   const long long m1 = rounds * n_cu / tiles_n * PT;
-  if (rounds < 1 || tiles % n_cu == 0 || m1 <= 0 || m1 >= M) return M;
+  if (rounds < 1 || tiles % n_cu == 0 || m1 < kPersistentRows || m1 >= M) return M;
   double rest = 0.0;
   pick_tile((int)(M - m1), N, K, false, n_cu, &rest);
   return tile_us(kPersistent, (int)m1, N, K, n_cu) + rest + kSecondLaunchUs < tile_us(kPersistent, M, N, K, n_cu)

@@ -73,3 +73,17 @@ def test_every_choice_is_possible(plan):
             m1 = plan.plan_rows(M, N, K, 256)
             assert 0 < m1 <= M and (m1 == M or m1 % 256 == 0)
     assert seen == set(TILES)
+
+
+def test_split_rows_stay_on_the_persistent_kernel(plan):
+    """The rows split off for full rounds are rows the persistent kernel takes
+    (at least 2048): with wide outputs a round has fewer, and a smaller share
+    would run on the other kernels though charged as a persistent round."""
+    rng = random.Random(2)
+    split = 0
+    for _ in range(20000):
+        M, N, K = int(2 ** rng.uniform(11, 18)), 256 * rng.randrange(1, 65), 128 * rng.randrange(2, 65)
+        m1 = plan.plan_rows(M, N, K, 256)
+        split += m1 < M
+        assert m1 == M or m1 >= 2048, (M, N, K, m1)
+    assert split > 500
