@@ -321,8 +321,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring(const bf16* __restrict__ A
 // multiple of 256, short K): there the other block's MFMAs run through one
 // block's prologue, epilogue and barriers, which the ring kernel, alone on its
 // CU, does not have: 66500 rows of N 1152, K 384 143 us on the ring, 130 here;
-// N 384, K 128 38.7, 32.9. Sums in the order
-// of the other kernels.
+// N 384, K 128 38.7, 32.9. Also
+// for weights of 2^31 elements and more (64-bit addresses). Sums in the order of
+// the other kernels.
 constexpr int GM = 128, GN = 128, GK = kRingK, GLD = GK + 8;
 
 template <int EPI>
@@ -964,7 +965,7 @@ static hipError_t plain(const void* A, int lda, const void* Bt, const float* bia
 }
 
 bool gemm_ln_ok(int N, int K, int lda, int ldc) {
-  return N % 128 == 0 && K % kRingK == 0 && (long long)N * K < (1ll << 31) && lda % 8 == 0 && ldc % 8 == 0;
+  return N % 128 == 0 && K % kRingK == 0 && lda % 8 == 0 && ldc % 8 == 0;
 }
 
 hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const float* bias, const void* R, int ldr,
@@ -1025,8 +1026,7 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
                        (((uintptr_t)Bt & 15) == 0) && (((uintptr_t)C & 15) == 0) && (((uintptr_t)R & 15) == 0) &&
                        (((uintptr_t)bias & 15) == 0) && (((uintptr_t)ln.g & 15) == 0) &&
                        (((uintptr_t)ln.b & 15) == 0) && ((((uintptr_t)ln.a2 | (uintptr_t)ln.r2) & 15) == 0);
-  // (the weight's byte offsets have to fit 32 bits too)
-  const bool mfma = N % 128 == 0 && K % kRingK == 0 && (long long)N * K < (1ll << 31) && aligned;
+  const bool mfma = N % 128 == 0 && K % kRingK == 0 && aligned;
   if (ln.a2 && !mfma) return halves();
   if (!mfma)
     return plain<bf16>(A, lda, Bt, bias, R, ldr, C, ldc, M, N, K, epi, ln, s);

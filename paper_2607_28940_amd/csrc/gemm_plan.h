@@ -65,8 +65,11 @@ inline bool persistent_shape(int M, int N, int K, long long ld_max) {
 inline int pick_tile(int M, int N, int K, bool persistent, int n_cu, double* us = nullptr) {
   int best = kPair;
   double best_us = 1e30;
+  // the ring kernel's weight offsets, as the persistent kernel's, are 32-bit
+  // byte offsets
+  const bool wide = (long long)N * K >= (1ll << 31);
   for (int c = 0; c < kGemmTiles; ++c) {
-    if (c == kPersistent && !persistent) continue;
+    if (c == kPersistent ? !persistent : wide && c != kPair) continue;
     const double t = tile_us(c, M, N, K, n_cu);
     // of small tiles within 3% the smaller: inside a call its loads, spread over
     // more CUs, wait less (one user's call 97.6 us, 99.8 without)

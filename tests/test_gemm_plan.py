@@ -87,3 +87,11 @@ def test_split_rows_stay_on_the_persistent_kernel(plan):
         split += m1 < M
         assert m1 == M or m1 >= 2048, (M, N, K, m1)
     assert split > 500
+
+
+@pytest.mark.parametrize("M", [1, 300, 5000, 100000])
+@pytest.mark.parametrize("N,K", [(131072, 16384), (16384, 131072), (65536, 32768)])
+def test_weights_past_2_31_elements(plan, M, N, K):
+    """Only the pair kernel addresses the weight with 64 bits."""
+    assert N * K >= 2 ** 31 and tile(plan, M, N, K) == "pair"
+    assert tile(plan, M, N, K - 128) != "pair" or M > 300
