@@ -1,40 +1,16 @@
 """Tile choice of the bf16 products (csrc/gemm_plan.h), compiled for the host:
 shapes whose kernel was measured, and bounds of the persistent kernel's share
 of the rows."""
-import ctypes
-import os
 import random
-import subprocess
 
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-TILES = ["32x32", "32x64", "64x64", "64x128", "128x128", "pair", "persistent"]
-SRC = """
-#include "gemm_plan.h"
-extern "C" int plan_tile(int M, int N, int K, long long ld, int n_cu) {
-  return tx::pick_tile(M, N, K, tx::persistent_shape(M, N, K, ld), n_cu);
-}
-extern "C" int plan_rows(int M, int N, int K, int n_cu) { return tx::persistent_rows(M, N, K, n_cu); }
-"""
+from tests.plan_util import TILES, Plan
 
 
 @pytest.fixture(scope="module")
 def plan(tmp_path_factory):
-    d = tmp_path_factory.mktemp("plan")
-    (d / "plan.cpp").write_text(SRC)
-    out = str(d / "plan.so")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-Wno-unused-variable", "-shared", "-fPIC",
-                    "-I" + os.path.join(ROOT, "paper_2607_28940_amd", "csrc"), str(d / "plan.cpp"), "-o", out],
-                   check=True)
-    lib = ctypes.CDLL(out)
-    lib.plan_tile.argtypes = [ctypes.c_int] * 3 + [ctypes.c_longlong, ctypes.c_int]
-    lib.plan_rows.argtypes = [ctypes.c_int] * 4
-    return lib
-
-
-def tile(plan, M, N, K):
-    return TILES[plan.plan_tile(M, N, K, max(N, K), 256)]
+    return Plan(tmp_path_factory.mktemp("plan"))
 
 
 # (M, N, K): the kernel, and a slower one (us, each launch on operands of its own)
@@ -58,7 +34,7 @@ MEASURED = [
 
 @pytest.mark.parametrize("shape,want", MEASURED)
 def test_measured_choices(plan, shape, want):
-    assert tile(plan, *shape) == want
+    assert plan.tile(*shape) == want
 
 
 def test_every_choice_is_possible(plan):
@@ -66,11 +42,11 @@ def test_every_choice_is_possible(plan):
     seen = set()
     for _ in range(20000):
         M, N, K = int(2 ** rng.uniform(0, 18)), 128 * rng.randrange(1, 65), 64 * rng.randrange(1, 129)
-        t = tile(plan, M, N, K)
+        t = plan.tile(M, N, K)
         seen.add(t)
         if t == "persistent":
             assert N % 256 == 0 and K % 128 == 0 and K >= 256 and M >= 2048
-            m1 = plan.plan_rows(M, N, K, 256)
+            m1 = plan.rows(M, N, K)
             assert 0 < m1 <= M and (m1 == M or m1 % 256 == 0)
     assert seen == set(TILES)
 
@@ -83,7 +59,7 @@ def test_split_rows_stay_on_the_persistent_kernel(plan):
     split = 0
     for _ in range(20000):
         M, N, K = int(2 ** rng.uniform(11, 18)), 256 * rng.randrange(1, 65), 128 * rng.randrange(2, 65)
-        m1 = plan.plan_rows(M, N, K, 256)
+        m1 = plan.rows(M, N, K)
         split += m1 < M
         assert m1 == M or m1 >= 2048, (M, N, K, m1)
     assert split > 500
@@ -93,5 +69,5 @@ def test_split_rows_stay_on_the_persistent_kernel(plan):
 @pytest.mark.parametrize("N,K", [(131072, 16384), (16384, 131072), (65536, 32768)])
 def test_weights_past_2_31_elements(plan, M, N, K):
     """Only the pair kernel addresses the weight with 64 bits."""
-    assert N * K >= 2 ** 31 and tile(plan, M, N, K) == "pair"
-    assert tile(plan, M, N, K - 128) != "pair" or M > 300
+    assert N * K >= 2 ** 31 and plan.tile(M, N, K) == "pair"
+    assert plan.tile(M, N, K - 128) != "pair" or M > 300

@@ -1,16 +1,18 @@
 """The projection kernels at the edges of their tiles: one request scored with
-its first C candidates, C on both sides of every tile height (32, 64, 128 rows
-and the persistent kernel's 256) and at one row, for models whose projections
-have 2, 3, 4, 8 and 32 k steps (the ring of stages shorter than its depth, odd,
-and longer). Every tile sums an output in the same order, so each score equals,
-bitwise, the one of the whole candidate set; that one is checked against the
-oracle within the bf16 bar."""
+its first C candidates, C on both sides of the tile heights (32, 64, 128 and 256
+rows) and at one row, for models whose projections have 2 to 32 k steps. Every
+tile sums an output in the same order, so each score equals, bitwise, the one of
+the whole candidate set; that one is checked against the oracle within the bf16
+bar. Which tile a product takes is the choice of csrc/gemm_plan.h, compiled for
+the host here: test_k_steps_of_every_tile says which pairs of tile and k steps
+its calls reach."""
 import numpy as np
 import pytest
 
 from paper_2607_28940_amd import inputs as I
 from paper_2607_28940_amd.inputs import ModelConfig
 from tests.parity_util import BF16_TOL, FP32_TOL, DeviceCase, check_err, log, oracle_request, score_err
+from tests.plan_util import RING_STAGES, Plan
 
 pytestmark = pytest.mark.gpu
 
@@ -38,6 +40,61 @@ def test_score_independent_of_tile(oracle_mod, name):
     n = 300
     err = score_err(base[:n], oracle_request(oracle_mod.Oracle(model, w), wl, 0, cand=Xc[:n])[0])
     log(f"gemm tiles {name}: max err {err['max']:.3e} p99 {err['p99']:.3e}")
+    check_err(err, BF16_TOL)
+
+
+# Ring depths are 16, 6, 4, 6 and 4 stages (32x32 to 128x128): k steps fewer than
+# half the depth, half, fewer than it, and more than it, odd and even
+STEPS = {"k2": (ModelConfig(128, 1, 1088, 1, 1, rel_pos_buckets=16), (20, 900, 2600, 4000, 6000, 8200)),
+         "k3": (ModelConfig(192, 3, 384, 1, 1, rel_pos_buckets=16), (130, 300, 900, 8200)),
+         "k5": (ModelConfig(256, 2, 320, 1, 1, rel_pos_buckets=16), (20, 900, 2100, 8200)),
+         "k7": (ModelConfig(256, 2, 448, 1, 1, rel_pos_buckets=16), (20, 900, 2100, 8200)),
+         "k17": (ModelConfig(256, 2, 1088, 1, 1, rel_pos_buckets=16), (34, 900, 1300, 2100, 5000, 8200)),
+         "k8": (ModelConfig(512, 4, 2048, 1, 1, rel_pos_buckets=16), (600, 4095, 4096, 4097, 4351, 4352, 4353))}
+REACHED = {("32x32", "more, odd"), ("32x32", "fewer"), ("32x64", "more, odd"), ("32x64", "more, even"),
+           ("32x64", "half"), ("32x64", "fewer"), ("64x64", "half"), ("64x64", "fewer"), ("64x64", "all"),
+           ("64x64", "more, odd"), ("64x64", "more, even"), ("64x128", "more, odd"), ("64x128", "more, even"),
+           ("128x128", "half"), ("128x128", "fewer"), ("128x128", "all"), ("128x128", "more, odd"),
+           ("128x128", "more, even"), ("persistent", "rows at its tile"), ("persistent", "rows past its tile")}
+
+
+def _reached(plan):
+    seen = set()
+    for model, counts in STEPS.values():
+        d, F = model.d_model, model.d_ffn
+        for C in counts + (max(counts) + 200,):
+            for M, N, K in ((C + 3, 3 * d, d), (C, d, d), (C, F, d), (C, d, F)):
+                if N % 128 or K % 64:
+                    continue
+                nk = K // 64
+                for t, rows in plan.launches(M, N, K):
+                    if t in RING_STAGES:
+                        S = RING_STAGES[t]
+                        seen.add((t, "half" if nk == S // 2 else "fewer" if nk < S else "all" if nk == S
+                                  else "more, odd" if nk % 2 else "more, even"))
+                    elif t == "persistent":
+                        seen.add((t, "rows at its tile" if rows % 256 == 0 else "rows past its tile"))
+    return seen
+
+
+@pytest.mark.parametrize("name", STEPS)
+def test_k_steps_of_every_tile(oracle_mod, tmp_path, name):
+    import torch
+    torch.cuda.set_device(0)
+    assert REACHED <= _reached(Plan(tmp_path)), REACHED - _reached(Plan(tmp_path))
+    model, counts = STEPS[name]
+    n = max(counts) + 200
+    wl = I.custom_workload(model, cfg_id=94, L=[70], S=[3], C=[n])
+    w = I.make_weights(model, ("sharp", "affine"))
+    run = DeviceCase(wl, w)
+    run.build([0])
+    Xc = I.request_tokens(wl, 0, I.STREAM_CANDIDATES)
+    base = run.score([0], cand=[Xc])[0]
+    assert np.all(np.isfinite(base))
+    for C in counts:
+        assert np.array_equal(run.score([0], cand=[Xc[:C]])[0], base[:C]), C
+    err = score_err(base[-200:], oracle_request(oracle_mod.Oracle(model, w), wl, 0, cand=Xc[-200:])[0])
+    log(f"k steps {name}: max err {err['max']:.3e}")
     check_err(err, BF16_TOL)
 
 
