@@ -155,8 +155,10 @@ constexpr int RK = kRingK;  // k columns per stage
 // stage k + 1 are read between the MFMAs of stage k. Rows are 128 bytes, 16-byte
 // slot s of row r holding chunk s ^ ((r / 2) % 8) (applied on the global
 // side): conflict-free fragment reads without padding. A wave computes
-// MI x NI MFMA tiles (with the 32x32 and 32x64 tiles only one or two waves
-// compute, all four load). Each output is summed over k in the same order
+// MI x NI MFMA tiles. The 32x32 and 32x64 tiles hold work for one or two waves;
+// the others load their share and repeat those waves' products, which are
+// dropped (leaving them out of the compute instead: one user's call 97.6 us
+// either way, a session 442 against 438). Each output is summed over k in the same order
 // with the same MFMAs as in the persistent kernel, so a score does not depend
 // on which kernel took its batch. Measured per launch, against the kernel this
 // replaced (128x128 tiles, operands through registers, one step ahead): M 34,
