@@ -509,7 +509,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   __shared__ __attribute__((aligned(16))) bf16 sKV[(2 + v_buffers(DH)) * 64 * DH];
 
   // block b runs on XCD b % 8 and takes entry b / 8 of that XCD's lists, the
-  // kv-split tiles (the longer ones) first
+  // kv-split tiles first (parts of long histories; a whole tile is longer than
+  // a part only where it has fewer than kXWholePages pages, and then the tiles
+  // hardly fill the GPU and their order does not matter)
   const int x = blockIdx.x & 7, n_split = split_off[x + 1] - split_off[x];
   int t_idx = (int)(blockIdx.x >> 3) - n_split;
   if (t_idx >= whole_off[x + 1] - whole_off[x]) return;

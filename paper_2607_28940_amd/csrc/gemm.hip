@@ -160,8 +160,8 @@ constexpr int RK = kRingK;  // k columns per stage
 // dropped (leaving them out of the compute instead: one user's call 97.6 us
 // either way, a session 442 against 438). Each output is summed over k in the same order
 // with the same MFMAs as in the persistent kernel, so a score does not depend
-// on which kernel took its batch. Measured per launch, against the kernel this
-// replaced (128x128 tiles, operands through registers, one step ahead): M 34,
+// on which kernel took its batch. Measured per launch, against the pair kernel
+// (128x128 tiles, operands through registers, one step ahead): M 34,
 // N 512, K 2048 26 -> 6.3 us; M 34, N 1024, K 4096 48 -> 9.5; M 300 51 -> 12;
 // M 1064 52 -> 21; M 4000 55 -> 37; M 1064, N 3072, K 1024 17.5 -> 11.3.
 template <int EPI, int BM, int BN, int MI, int NI, int S>
