@@ -989,12 +989,27 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
                        epi, s, l2);
   };
   if (ln.a2 && (ln.m1 < 0 || ln.m1 > M || (epi_resid(epi) && !ln.r2))) return hipErrorInvalidValue;
+  auto row_range = [&](long long m0, int mc) {  // rows m0 .. m0 + mc - 1 of one array
+    LnResid lc = ln;
+    if (lc.stats) lc.stats += m0;
+    const size_t es = bf ? 2 : 4;
+    return launch_gemm(bf, (const char*)A + m0 * lda * es, lda, Bt, bias,
+                       R ? (const void*)((const char*)R + m0 * ldr * es) : nullptr, ldr, (char*)C + m0 * ldc * es, ldc,
+                       mc, N, K, epi, s, lc);
+  };
+  auto row_ranges = [&](long long rows_max) {
+    for (long long m0 = 0; m0 < M; m0 += rows_max) {
+      const hipError_t e = row_range(m0, (int)std::min(rows_max, (long long)M - m0));
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  };
   if (!bf) {
     // 16-byte operand loads: K a multiple of a chunk, rows and bases aligned (a
-    // caller's tokens may be aligned to 4 bytes only). The grid's y extent
-    // limits the rows.
-    if (K % 16 == 0 && lda % 4 == 0 && (((uintptr_t)A | (uintptr_t)Bt | (uintptr_t)ln.a2) & 15) == 0 &&
-        M <= 16 * 65535) {
+    // caller's tokens may be aligned to 4 bytes only)
+    if (K % 16 == 0 && lda % 4 == 0 && (((uintptr_t)A | (uintptr_t)Bt | (uintptr_t)ln.a2) & 15) == 0) {
+      constexpr int kGridRows = 16 * 65535;  // the grid's y extent
+      if (M > kGridRows) return ln.a2 ? halves() : row_ranges(kGridRows);
       const float *a = (const float*)A, *b = (const float*)Bt, *r = (const float*)R;
       if ((long long)((M + 31) / 32) * ((N + 31) / 32) >= 1024)  // four waves on each of 256 CUs
         return f32_mfma<2, 2>(a, lda, b, bias, r, ldr, (float*)C, ldc, M, N, K, epi, ln, s);
@@ -1003,26 +1018,12 @@ hipError_t launch_gemm(bool bf, const void* A, int lda, const void* Bt, const fl
     if (ln.a2) return halves();
     return plain<float>(A, lda, Bt, bias, R, ldr, C, ldc, M, N, K, epi, ln, s);
   }
-  auto row_range = [&](long long m0, int mc) {  // rows m0 .. m0 + mc - 1 of one array
-    LnResid lc = ln;
-    if (lc.stats) lc.stats += m0;
-    return launch_gemm(bf, (const bf16*)A + m0 * lda, lda, Bt, bias,
-                       R ? (const void*)((const bf16*)R + m0 * ldr) : nullptr, ldr, (bf16*)C + m0 * ldc, ldc, mc, N, K,
-                       epi, s, lc);
-  };
   // The MFMA kernels address A, R and C with 32-bit byte offsets: a product
   // whose operands span 2^31 elements or more runs as several row chunks.
   {
     const long long ld_max = std::max({(long long)lda, (long long)ldc, epi_resid(epi) ? (long long)ldr : 1ll});
     const long long rows_max = std::max(256ll, ((1ll << 31) - 1) / ld_max / 256 * 256);
-    if (M > rows_max && ln.a2) return halves();
-    if (M > rows_max) {
-      for (long long m0 = 0; m0 < M; m0 += rows_max) {
-        const hipError_t e = row_range(m0, (int)std::min(rows_max, (long long)M - m0));
-        if (e != hipSuccess) return e;
-      }
-      return hipSuccess;
-    }
+    if (M > rows_max) return ln.a2 ? halves() : row_ranges(rows_max);
   }
   const bool aligned = (lda % 8 == 0) && (ldc % 8 == 0) && (ldr % 8 == 0) && (((uintptr_t)A & 15) == 0) &&
                        (((uintptr_t)Bt & 15) == 0) && (((uintptr_t)C & 15) == 0) && (((uintptr_t)R & 15) == 0) &&

@@ -194,3 +194,21 @@ def test_tokens_in_place_or_copied(name, model, S, C):
     a = run.cache.score([0], xs, [0, S], xc, [0, C]).cpu().numpy()
     b = run.cache.score([0], off(xs), [0, S], off(xc), [0, C]).cpu().numpy()
     assert np.all(np.isfinite(a)) and np.array_equal(a, b)
+
+
+def test_f32_rows_past_the_grid():
+    """fp32 calls of more rows than one launch's grid covers (65535 blocks of 16
+    rows) run in row ranges on the same kernel: scores bitwise as in small calls."""
+    import torch
+    torch.cuda.set_device(0)
+    model = F32["d64"]
+    C = 16 * 65535 + 1000
+    wl = I.custom_workload(model, cfg_id=95, L=[70], S=[3], C=[1])
+    run = DeviceCase(wl, I.make_weights(model, ("sharp", "affine")))
+    run.build([0])
+    xs = run.dev(I.request_tokens(wl, 0, I.STREAM_SERVING))
+    xc = torch.randn((C, model.d_model), generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+    base = run.cache.score([0], xs, [0, 3], xc, [0, C])
+    for a, b in ((0, 300), (16 * 65535 - 200, 16 * 65535 + 200), (C - 300, C)):
+        part = run.cache.score([0], xs, [0, 3], xc[a:b].contiguous(), [0, b - a])
+        assert torch.isfinite(part).all() and torch.equal(part, base[a:b]), (a, b)
